@@ -29,8 +29,9 @@ PER_FILE = {
     # MFMA accumulators in ordinary VGPRs: the attention kernel fits in 256 of them, and
     # the AGPR form would copy its accumulators back and forth around every softmax
     "attn.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
+    "attn_f32.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
 }
-SOURCES = ["topk.hip", "select.hip", "attn.hip", "walk.hip", "commit.hip", "layer.hip",
+SOURCES = ["topk.hip", "select.hip", "attn.hip", "attn_f32.hip", "walk.hip", "commit.hip", "layer.hip",
            "noalloc.hip", "api.cpp"]
 
 

@@ -172,7 +172,10 @@ taps_status tree_verify_attn_validate(int32_t batch, int32_t budget, int32_t Hq,
 size_t tree_verify_attn_workspace_bytes(int32_t batch, int32_t budget, int32_t Hq, int32_t Hkv,
                                         int32_t head_dim, int32_t max_ctx, int32_t dtype) {
   if (attn_check(batch, budget, Hq, Hkv, head_dim, max_ctx, dtype, 1.0f) != TAPS_OK) return 0;
-  if (dtype == TAPS_FP32 || batch == 0) return 0;
+  if (batch == 0) return 0;
+  if (dtype == TAPS_FP32)
+    return attn_f32_ws_bytes(plan_attn_f32(batch, budget, Hq, Hkv, head_dim, max_ctx), batch, Hkv,
+                             head_dim);
   const AttnPlan pl = plan_attn(batch, budget, Hq, Hkv, head_dim, max_ctx);
   return attn_ws_bytes(pl, batch, budget, Hq, Hkv, head_dim);
 }
@@ -192,9 +195,13 @@ taps_status tree_verify_attn_timed(const void* Q_tree, const void* K_cache, cons
   const uintptr_t align_or = (uintptr_t)Q_tree | (uintptr_t)K_cache | (uintptr_t)V_cache | (uintptr_t)O;
   if ((align_or & 15) != 0) return TAPS_ERR_INVALID_ARG;
   if (dtype == TAPS_FP32) {
+    // the scratch is optional: without it the keys are not split
+    AttnF32Plan p = plan_attn_f32(batch, budget, Hq, Hkv, head_dim, max_ctx);
+    if (!ws || ((uintptr_t)ws & 15) != 0 || ws_bytes < attn_f32_ws_bytes(p, batch, Hkv, head_dim))
+      p.splits = 1;
     return launch_attn_f32((const float*)Q_tree, (const float*)K_cache, (const float*)V_cache,
                            kv_offset, ctx_len, tree_parent, n_nodes, batch, budget, Hq, Hkv,
-                           head_dim, max_ctx, scale, (float*)O, stream, ev_begin,
+                           head_dim, max_ctx, scale, p, (float*)O, ws, stream, ev_begin,
                            ev_end) == hipSuccess
                ? TAPS_OK
                : TAPS_ERR_HIP;

@@ -16,7 +16,7 @@
 //     split reaches the tree rows; keys beyond the split or outside the mask get -inf;
 //   * fp32 online softmax in base 2; each split writes unnormalised O, its running max
 //     and its sum; a second kernel combines the splits and rounds to bf16.
-// fp32 path: a plain VALU kernel, one workgroup per (request, node, query head).
+// (fp32 inputs: attn_f32.hip.)
 #include <algorithm>
 #include <cstdio>
 #include <cstdlib>
@@ -35,8 +35,6 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 
-constexpr int kThreads = 256;
-constexpr int kWavesA = 4;
 constexpr int kKT = 64;  // keys per tile
 constexpr float kLog2e = 1.4426950408889634f;
 
@@ -1258,89 +1256,6 @@ __global__ __launch_bounds__(kCombineThreads) void attn_combine_kernel(
   *(uint4*)(O + (((size_t)b * N + i) * Hq + hq) * HD + d) = make_uint4(lo.x, lo.y, hi.x, hi.y);
 }
 
-// ---------------------------------------------------------------- fp32 VALU path
-template <int HD>
-__global__ __launch_bounds__(kThreads) void attn_f32_kernel(
-    const float* __restrict__ Q, const float* __restrict__ Kc, const float* __restrict__ Vc,
-    const int64_t* __restrict__ offp, const int32_t* __restrict__ ctxp,
-    const int32_t* __restrict__ parentp, const int32_t* __restrict__ nnp, int N, int Hq,
-    int Hkv, int max_ctx, float scale, float* __restrict__ O) {
-  constexpr int GROUPS = kThreads / HD;  // key groups for the P.V accumulation
-  __shared__ float s_q[HD];
-  __shared__ float s_p[kThreads];
-  __shared__ float s_red[kThreads / 64];
-  __shared__ uint64_t s_anc[kAncWords];
-  __shared__ float s_acc[GROUPS][HD];
-  const int i = blockIdx.x, hq = blockIdx.y, b = blockIdx.z;
-  const int tid = threadIdx.x;
-  const int n = min(max(nnp[b], 0), N);
-  if (i >= n) return;
-  const int ctx = min(max(ctxp[b], 0), max_ctx);
-  const int R = ctx + n;
-  const int G = Hq / Hkv, g = hq / G;
-  const int64_t kv0 = offp[b];
-  const size_t rs = (size_t)Hkv * HD;
-  if (tid < HD) s_q[tid] = Q[(((size_t)b * N + i) * Hq + hq) * HD + tid];
-  if (tid == 0) {
-    uint64_t a[kAncWords];
-    const int32_t* pp = parentp + (size_t)b * N;
-    ancestor_mask(i, [&](int j) { return pp[j]; }, a);
-    for (int w = 0; w < kAncWords; ++w) s_anc[w] = a[w];
-  }
-  __syncthreads();
-  float m_run = -INFINITY, l_run = 0.f, acc = 0.f;
-  const int dd = tid % HD, grp = tid / HD;
-  for (int k0 = 0; k0 < R; k0 += kThreads) {
-    const int key = k0 + tid;
-    float sc = -INFINITY;
-    bool ok = key < R;
-    if (ok && key >= ctx) {
-      const int t = key - ctx;
-      ok = (s_anc[t >> 6] >> (t & 63)) & 1ull;
-    }
-    if (ok) {
-      const float* kr = Kc + (size_t)(kv0 + key) * rs + (size_t)g * HD;
-      float dot = 0.f;
-      for (int d = 0; d < HD; ++d) dot += s_q[d] * kr[d];
-      sc = dot * scale;
-    }
-    // tile max
-    float mx = sc;
-    for (int off = 32; off >= 1; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
-    if ((tid & 63) == 0) s_red[tid >> 6] = mx;
-    __syncthreads();
-    mx = s_red[0];
-    for (int w = 1; w < kThreads / 64; ++w) mx = fmaxf(mx, s_red[w]);
-    __syncthreads();
-    const float m_new = fmaxf(m_run, mx);
-    const float ref = m_new == -INFINITY ? 0.f : m_new;
-    const float pv = ok ? expf(sc - ref) : 0.f;
-    s_p[tid] = pv;
-    float sum = pv;
-    for (int off = 32; off >= 1; off >>= 1) sum += __shfl_xor(sum, off);
-    if ((tid & 63) == 0) s_red[tid >> 6] = sum;
-    __syncthreads();
-    sum = 0.f;
-    for (int w = 0; w < kThreads / 64; ++w) sum += s_red[w];
-    const float alpha = expf(m_run - ref);
-    l_run = l_run * alpha + sum;
-    acc *= alpha;
-    m_run = m_new;
-    for (int j = grp; j < kThreads && k0 + j < R; j += GROUPS) {
-      const float pj = s_p[j];
-      if (pj != 0.f) acc += pj * Vc[(size_t)(kv0 + k0 + j) * rs + (size_t)g * HD + dd];
-    }
-    __syncthreads();
-  }
-  s_acc[grp][dd] = acc;
-  __syncthreads();
-  if (tid < HD) {
-    float t = 0.f;
-    for (int gi = 0; gi < GROUPS; ++gi) t += s_acc[gi][tid];
-    O[(((size_t)b * N + i) * Hq + hq) * HD + tid] = t / l_run;
-  }
-}
-
 }  // namespace
 
 AttnPlan plan_attn(int batch, int budget, int Hq, int Hkv, int head_dim, int max_ctx,
@@ -1533,21 +1448,5 @@ hipError_t launch_attn_bf16_paged(const void* Q, const void* K_pages, const void
 }
 
 int paged_max_split(int page_shift) { return (kPageSlots - 1) << page_shift; }
-
-hipError_t launch_attn_f32(const float* Q, const float* K, const float* V, const int64_t* off,
-                           const int32_t* ctx, const int32_t* parent, const int32_t* n,
-                           int batch, int budget, int Hq, int Hkv, int head_dim, int max_ctx,
-                           float scale, float* O, hipStream_t s, hipEvent_t ev_begin,
-                           hipEvent_t ev_end) {
-  if (batch <= 0) return hipSuccess;
-  dim3 grid((unsigned)budget, (unsigned)Hq, (unsigned)batch), block(kThreads);
-  if (head_dim == 128)
-    hipExtLaunchKernelGGL(attn_f32_kernel<128>, grid, block, 0, s, ev_begin, ev_end, 0, Q, K, V,
-                          off, ctx, parent, n, budget, Hq, Hkv, max_ctx, scale, O);
-  else
-    hipExtLaunchKernelGGL(attn_f32_kernel<64>, grid, block, 0, s, ev_begin, ev_end, 0, Q, K, V,
-                          off, ctx, parent, n, budget, Hq, Hkv, max_ctx, scale, O);
-  return hipGetLastError();
-}
 
 }  // namespace taps

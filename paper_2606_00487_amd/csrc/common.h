@@ -100,11 +100,19 @@ hipError_t launch_attn_bf16_paged(const void* Q, const void* K_pages, const void
 // longest split a paged call may take: its page ids must fit the kernel's table
 int paged_max_split(int page_shift);
 
+// fp32: K and V split over `splits` workgroups of eight waves per 16 query rows; the scratch
+// holds the splits' parts (none for one split)
+struct AttnF32Plan {
+  int splits;
+  int rtiles;   // 16-row tiles of a KV head's budget * G query rows
+};
+AttnF32Plan plan_attn_f32(int batch, int budget, int Hq, int Hkv, int head_dim, int max_ctx);
+size_t attn_f32_ws_bytes(const AttnF32Plan& p, int batch, int Hkv, int head_dim);
 hipError_t launch_attn_f32(const float* Q, const float* K, const float* V, const int64_t* off,
                            const int32_t* ctx, const int32_t* parent, const int32_t* n,
                            int batch, int budget, int Hq, int Hkv, int head_dim, int max_ctx,
-                           float scale, float* O, hipStream_t s, hipEvent_t ev_begin = nullptr,
-                           hipEvent_t ev_end = nullptr);
+                           float scale, const AttnF32Plan& p, float* O, void* ws, hipStream_t s,
+                           hipEvent_t ev_begin = nullptr, hipEvent_t ev_end = nullptr);
 
 hipError_t launch_walk(const taps_tree& t, int batch, int budget, int block,
                        const int32_t* target, int32_t* path, int32_t* path_len, int32_t* bonus,
