@@ -432,12 +432,9 @@ __global__ __launch_bounds__(256) void attn_bf16_w4_kernel(
 // Eight waves per workgroup (two per SIMD), in two key groups of four: group g works on
 // the 32-key stages g, g + 2, g + 4, ... of the split, each wave on 32 query rows, and
 // the groups merge their results through LDS at the end.  K and V cycle through rings of
-// eight 32-key slots (sixteen separate LDS objects): step t processes stages 2t and
-// 2t + 1 and issues the loads of V(2t + 6), V(2t + 7), K(2t + 8) and K(2t + 9), so every
-// load has three steps to arrive.  Within a group the pipeline is the same as in the
-// four-wave kernel: the softmax and P V of a stage run together with the MFMAs of S for
-// the group's next stage.  The step loop is written once per group (template) and
-// unrolled by four, so that every LDS access names its slot statically.
+// eight 32-key slots.  Their 16-byte chunks are XOR-permuted by kswz16, which measures
+// 256 B/clk per CU for the K reads and 201 for the transposing V reads (three-bit kswz: 128
+// for both).
 // Division of small non-negative ints by the launch's tile, split, head and group
 // counts: floor(n / d) = high half of n * ceil(2^32 / d), exact for n < 2^32 / d (the
 // rounding term of the multiplier adds less than n / 2^32 < 1/d to n / d)
@@ -621,10 +618,7 @@ __device__ __attribute__((always_inline)) inline void attn_bf16_body(
   static_assert(TILEB == 8 * BLK, "one direct load per wave and slot");
   static_assert(NT >= TAPS_MAX_BUDGET, "one parent pointer per thread");
   static_assert(TAPS_MAX_BUDGET <= 8 * 64, "the eight waves load 64 parent pointers each");
-  __shared__ __attribute__((aligned(16))) unsigned char s_k0[TILEB], s_k1[TILEB], s_k2[TILEB],
-      s_k3[TILEB], s_k4[TILEB], s_k5[TILEB], s_k6[TILEB], s_k7[TILEB];
-  __shared__ __attribute__((aligned(16))) unsigned char s_v0[TILEB], s_v1[TILEB], s_v2[TILEB],
-      s_v3[TILEB], s_v4[TILEB], s_v5[TILEB], s_v6[TILEB], s_v7[TILEB];
+  __shared__ __attribute__((aligned(16))) unsigned char s_k[8 * TILEB], s_v[8 * TILEB];
   __shared__ uint64_t s_anc[MT + 1][kAncWords];   // masks of this tile's nodes
   __shared__ int s_par[TAPS_MAX_BUDGET];
   __shared__ float2 s_ml[8 * 64];
@@ -660,14 +654,15 @@ __device__ __attribute__((always_inline)) inline void attn_bf16_body(
                                       split_len, pair, tab,
                                       pair == 0 && mt == 0 && (threadIdx.x >> 6) == 0);
     if (!rp.found) return;   // past the batch's pairs (nothing issued yet)
-    b = rp.b;
-    g = rp.g;
-    split = rp.split;
-    split_len = rp.L;
+    b = __builtin_amdgcn_readfirstlane(rp.b);
+    g = __builtin_amdgcn_readfirstlane(rp.g);
+    split = __builtin_amdgcn_readfirstlane(rp.split);
+    split_len = __builtin_amdgcn_readfirstlane(rp.L);
   }
   const int G = dm.div(Hq, Hkv, dm.hk);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int rg = wave & 3, kg = wave >> 2;
+  const int wave_u = __builtin_amdgcn_readfirstlane(wave);   // uniform: scalar branches
+  const int rg = wave_u & 3, kg = wave_u >> 2;
   const int l32 = lane & 31, hl = lane >> 5;
   const int row0 = mt * MT;
 
@@ -678,19 +673,17 @@ __device__ __attribute__((always_inline)) inline void attn_bf16_body(
   // (row0 + r) / G, query head g * G + (row0 + r) % G) is in V slot 4 + r / 32, its 16-byte
   // chunks XOR-permuted by kswz16(r % 32); wave (rg, kg) loads rows rg * 32 + kg * 16 ..
   // + 15, four rows (1 KB) per load.
-  const int wave_u = __builtin_amdgcn_readfirstlane(wave);
-  const int rg_u = wave_u & 3, kg_u = wave_u >> 2;
-  unsigned char* const qslot = rg_u == 0 ? s_v4 : rg_u == 1 ? s_v5 : rg_u == 2 ? s_v6 : s_v7;
+  unsigned char* const qslot = s_v + (4 + rg) * TILEB;
   {
     const i32x4 qrs = buffer_rsrc(Q + (size_t)b * N * Hq * HD, (uint32_t)((size_t)N * Hq * HD * 2));
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      const int r = kg_u * 16 + 4 * j + (lane >> 4);   // row within the slot
-      const int qr = min(row0 + rg_u * 32 + r, N * G - 1);
+      const int r = kg * 16 + 4 * j + (lane >> 4);   // row within the slot
+      const int qr = min(row0 + rg * 32 + r, N * G - 1);
       const int node = dm.div(qr, G, dm.g);
       const uint32_t off = (uint32_t)(node * Hq + g * G + (qr - node * G)) * (HD * 2) +
                            16u * (uint32_t)((lane & 15) ^ kswz16(r));
-      load_lds16(qrs, qslot + (kg_u * 16 + 4 * j) * ROWB, off);
+      load_lds16(qrs, qslot + (kg * 16 + 4 * j) * ROWB, off);
     }
     if (wave_u < TAPS_MAX_BUDGET / 64)
       load_lds4(buffer_rsrc(parentp + (size_t)b * N, (uint32_t)N * 4),
@@ -733,8 +726,8 @@ __device__ __attribute__((always_inline)) inline void attn_bf16_body(
   } else {
     load_request_scalars(ctxp + b, nnp + b, offp + b, ctx_raw, n_raw, kv0);
   }
-  const int ctx = min(max(ctx_raw, 0), max_ctx);
-  const int n = min(max(n_raw, 0), N);
+  const int ctx = __builtin_amdgcn_readfirstlane(min(max(ctx_raw, 0), max_ctx));
+  const int n = __builtin_amdgcn_readfirstlane(min(max(n_raw, 0), N));
   const int R = ctx + n;
   const int k_begin = split * split_len;
   const int k_end = min(R, k_begin + split_len);
@@ -773,10 +766,10 @@ __device__ __attribute__((always_inline)) inline void attn_bf16_body(
     const int rb = wave_u * BLK + lane * 16;
     const int kr = rb / ROWB;
     const int pc = (rb - kr * ROWB) / 16;
-    ld_off = (uint32_t)kr * rsb + (uint32_t)((pc ^ kswz(kr)) * 16);
+    ld_off = (uint32_t)kr * rsb + (uint32_t)((pc ^ kswz16(kr)) * 16);
   }
-  // paged steps: waves 2q and 2q + 1 load all of the step's q-th stage, blocks 4 (w & 1) ..
-  // 4 (w & 1) + 3 each, so that a wave builds one resource per step instead of four
+  // paged: two waves load a whole slot, blocks 4 (w & 1) .. 4 (w & 1) + 3 each, so that a
+  // wave builds one resource in every other phase instead of two in each
   uint32_t pg_off[4] = {0u, 0u, 0u, 0u};
   if constexpr (PAGED) {
 #pragma unroll
@@ -784,7 +777,7 @@ __device__ __attribute__((always_inline)) inline void attn_bf16_body(
       const int rb = (4 * (wave_u & 1) + b) * BLK + lane * 16;
       const int kr = rb / ROWB;
       const int pc = (rb - kr * ROWB) / 16;
-      pg_off[b] = (uint32_t)kr * rsb + (uint32_t)((pc ^ kswz(kr)) * 16);
+      pg_off[b] = (uint32_t)kr * rsb + (uint32_t)((pc ^ kswz16(kr)) * 16);
     }
   }
   // contiguous: the stage's offset goes into the per-lane offset, which the buffer range
@@ -794,10 +787,13 @@ __device__ __attribute__((always_inline)) inline void attn_bf16_body(
   // here is uniform over the workgroup and kept in scalar registers.
   const int kb_u = __builtin_amdgcn_readfirstlane(k_begin);
   const int ke_u = __builtin_amdgcn_readfirstlane(k_end);
-  auto issue_at = [&](const auto& src, unsigned char* buf, int s, int pg)
+  // (buf: the slot's LDS address)
+  const uint32_t s_k0 = __builtin_amdgcn_readfirstlane(lds_address(s_k));
+  const uint32_t s_v0 = __builtin_amdgcn_readfirstlane(lds_address(s_v));
+  auto issue_at = [&](const auto& src, uint32_t buf, int s, int pg)
                       __attribute__((always_inline)) {
     if constexpr (!PAGED) {
-      load_lds16(src, buf + wave_u * BLK, ld_off + (uint32_t)(s * KT) * rsb);
+      load_lds16_at(src, buf + wave_u * BLK, ld_off + (uint32_t)(s * KT) * rsb);
     } else {
       // a stage with no rows left gets an empty resource and touches no memory, whatever
       // its page; the host keeps num_pages * page_rows below 2^32 (prow fits 32 bits)
@@ -811,7 +807,7 @@ __device__ __attribute__((always_inline)) inline void attn_bf16_body(
       r[1] = __builtin_amdgcn_readfirstlane((int)(uint32_t)(a >> 32));
       r[2] = __builtin_amdgcn_readfirstlane((int)((uint32_t)rows * rsb));
       r[3] = 0x00020000;
-      load_lds16(r, buf + wave_u * BLK, ld_off);
+      load_lds16_at(r, buf + wave_u * BLK, ld_off);
     }
   };
   // paged: the page of stage s < 4 (taken with the request's sizes) ...
@@ -828,14 +824,14 @@ __device__ __attribute__((always_inline)) inline void attn_bf16_body(
       v[q] = s_pg[min((r0 >> pk.page_shift) - pi0, kPageSlots - 1)];
     }
   };
-  auto issue = [&](const auto& src, unsigned char* buf, int s) __attribute__((always_inline)) {
+  auto issue = [&](const auto& src, uint32_t buf, int s) __attribute__((always_inline)) {
     issue_at(src, buf, s, PAGED ? first_page(s) : 0);
   };
   auto page_of_stage = [&](int st) -> int {
     return s_pg[min(((kb_u + st * KT) >> pk.page_shift) - pi0, kPageSlots - 1)];
   };
   // paged: this wave's four blocks of stage st (page pg) into slot buf
-  auto issue4_paged = [&](uint64_t src, unsigned char* buf, int st, int pg)
+  auto issue4_paged = [&](uint64_t src, uint32_t buf, int st, int pg)
                           __attribute__((always_inline)) {
     const int r0 = kb_u + st * KT;
     const int rows = min(max(ke_u - r0, 0), KT);
@@ -849,15 +845,16 @@ __device__ __attribute__((always_inline)) inline void attn_bf16_body(
     r[3] = 0x00020000;
 #pragma unroll
     for (int b = 0; b < 4; ++b)
-      load_lds16(r, buf + (4 * (wave_u & 1) + b) * BLK, pg_off[b]);
+      load_lds16_at(r, buf + (4 * (wave_u & 1) + b) * BLK, pg_off[b]);
   };
 
   const bool tree_split = k_end > ctx;
-  // K(0) K(1) and the loads of step -3 [V(2t+6) V(2t+7) K(2t+8) K(2t+9)] now; those of
-  // steps -2 and -1 after the first S (so its reads of K(0), K(1) wait for nothing else)
+  // K(0) K(1), then the loads of phases -6 and -5 [V(p+6) K(p+8)]; those of phases -4 .. -1
+  // once K(0) and K(1) have been read (so that those reads wait for nothing else)
   issue(krs, s_k0, 0);
-  issue(krs, s_k1, 1);
-  issue(vrs, s_v0, 0); issue(vrs, s_v1, 1); issue(krs, s_k2, 2); issue(krs, s_k3, 3);
+  issue(krs, s_k0 + TILEB, 1);
+  issue(vrs, s_v0, 0); issue(krs, s_k0 + 2 * TILEB, 2);
+  issue(vrs, s_v0 + TILEB, 1); issue(krs, s_k0 + 3 * TILEB, 3);
   TAPS_WAIT_VMCNT(6);   // queries and parents: this wave's part
   TAPS_LDS_BARRIER();   // ... and every other wave's part (the K/V loads stay in flight)
   bf16x8 q[NKK];        // queries of this lane: B operand of S^T = K Q^T
@@ -877,43 +874,77 @@ __device__ __attribute__((always_inline)) inline void attn_bf16_body(
     TAPS_LDS_BARRIER();
   }
 
-  // ---- per-lane LDS read offsets
-  const int fk = kswz(l32);
-  int koff[4];
+  // ---- per-lane LDS read offsets.  Chunk c of key row r sits at chunk c ^ kswz16(r).
+  // K: row l32, chunks 2 kk + hl
+  // (LDS addresses in slot 0, opaque to the compiler so that the slots are constant offsets)
+  typedef __attribute__((address_space(3))) unsigned char lds_u8;
+  typedef __attribute__((address_space(3))) bf16x8 lds_bf16x8;
+  const int fk = kswz16(l32);
+  uint32_t koff[NKK];
 #pragma unroll
-  for (int j = 0; j < 4; ++j) koff[j] = l32 * ROWB + 32 * (j ^ (fk >> 1)) + 16 * (hl ^ (fk & 1));
+  for (int kk = 0; kk < NKK; ++kk) {
+    koff[kk] = (uint32_t)(uintptr_t)(lds_u8*)s_k + kg * TILEB + l32 * ROWB + 16 * ((2 * kk + hl) ^ fk);
+    asm volatile("" : "+v"(koff[kk]));
+  }
+  // V^T: lanes 4t + q of each 16-lane group read row 4 hl + t (and 8 rows further down), 8
+  // bytes at d = 32 db + 16 g16 + 4 q, i.e. in chunk 4 db + 2 g16 + q / 2
   const int g16 = (lane >> 4) & 1, tq = (lane & 15) >> 2, qq = lane & 3;
-  const int fv = kswz(4 * hl + tq);
-  int voff[2];
+  uint32_t voff[2][NDB];
 #pragma unroll
-  for (int j = 0; j < 2; ++j)
-    voff[j] = (4 * hl + tq) * ROWB + 8 * (qq & 1) + 16 * ((g16 * 2 + (qq >> 1)) ^ (fv & 3)) +
-              64 * (j ^ (fv >> 2));
-
-  // S^T of the 32 keys in K slot kbuf, one k-step
-  auto s_mfma = [&](const unsigned char* kbuf, int kk, f32x16& s) __attribute__((always_inline)) {
-    const bf16x8 a = *(const bf16x8*)(kbuf + 32 * (kk & ~3) + koff[kk & 3]);
-    if (kk == 0) {
-      f32x16 z;
+  for (int h8 = 0; h8 < 2; ++h8)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) z[v] = 0.f;
-      s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, q[kk], z, 0, 0, 0);
-    } else {
-      s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, q[kk], s, 0, 0, 0);
+    for (int db = 0; db < NDB; ++db) {
+      const int r = 8 * h8 + 4 * hl + tq;
+      voff[h8][db] = (uint32_t)(uintptr_t)(lds_u8*)s_v + kg * TILEB + r * ROWB + 8 * (qq & 1) +
+                     16 * ((4 * db + 2 * g16 + (qq >> 1)) ^ kswz16(r));
+      asm volatile("" : "+v"(voff[h8][db]));
     }
-  };
 
   f32x16 o[NDB];
 #pragma unroll
   for (int db = 0; db < NDB; ++db)
 #pragma unroll
     for (int v = 0; v < 16; ++v) o[db][v] = 0.f;
-  float m_ref = -INFINITY, l_run = 0.f;
+  // softmax reference m_ref (base 2; m_neg = -m_ref or 0), moved when a score exceeds m_thr,
+  // i.e. the reference by more than 2^8
+  float m_ref = -INFINITY, l_run = 0.f, m_thr = -INFINITY, m_neg = 0.f;
+  const float thr8 = 8.f / scale_log2;   // scale > 0
 
-  // Softmax of S (keys base .. base + 31) and O^T += V^T P^T from V slot vbuf, with the
-  // MFMAs of the group's next S from K slot knext interleaved
-  auto softmax_pv = [&](f32x16& sc, const unsigned char* vbuf, const unsigned char* knext,
-                        f32x16& sn, int base) __attribute__((always_inline)) {
+  // ---- The two waves of a SIMD (one of each key group) alternate between a matrix phase
+  // and a softmax phase, half a step apart, so that one keeps the matrix cores busy while the
+  // other has the vector unit.  Stage t of a group:
+  //   matrix phase   S^T(t) = K(t) Q^T, O^T += V(t-1)^T P(t-1)^T: the operands are in
+  //                  registers, and each is replaced by the next one's (K(t+1), V(t)) as soon
+  //                  as its MFMA has been issued, so the LDS reads hide behind the MFMAs;
+  //   softmax phase  S(t) -> P(t): vector work alone.  Beside a busy matrix core a vector
+  //                  instruction takes 6 cycles and an exponential 11 (a microbenchmark), so
+  //                  this phase, about 75 of them, is the longer one: the slots are constant
+  //                  offsets (the loop is unrolled by four) and nothing else is left in it.
+  // Measured against the two waves in the same phase with their operands read before each
+  // pair of MFMAs: 16 requests of 512-16K keys 228 -> 205 us, 4 x 32K keys over pages
+  // 612 -> 577 us, one request of 128 nodes and 32K keys 83 -> 71 us (calls with the combine).
+  // The reads in the softmax phase instead: 218, 588 and 76 us.
+  bf16x8 ka[NKK], va[2][NDB], pg[2];
+  f32x16 sc;
+  auto read_k = [&](int slot, int kk) __attribute__((always_inline)) {
+    ka[kk] = *(const lds_bf16x8*)(koff[kk] + slot * TILEB);
+  };
+  auto read_v = [&](int slot, int hf, int db) __attribute__((always_inline)) {
+    // (16 rows further down the permutation is the same)
+    const uint32_t at = (uint32_t)slot * TILEB + (16 * hf) * ROWB;
+    const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)(voff[0][db] + at));
+    const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)(voff[1][db] + at));
+    va[hf][db] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+  };
+  auto mul_pv = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int hf = 0; hf < 2; ++hf)
+#pragma unroll
+      for (int db = 0; db < NDB; ++db)
+        o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[hf][db], pg[hf], o[db], 0, 0, 0);
+  };
+  // S (keys base .. base + 31) -> P
+  auto softmax = [&](int base) __attribute__((always_inline)) {
     const bool need_mask = base + KT > ctx || base + KT > k_end;
     if (need_mask) {
       const uint64_t win =
@@ -926,106 +957,134 @@ __device__ __attribute__((always_inline)) inline void attn_bf16_body(
         sc[v] = ok ? sc[v] : -INFINITY;
       }
     }
+    float mx = fmaxf(sc[0], sc[1]), my = fmaxf(sc[8], sc[9]);
 #pragma unroll
-    for (int kk = 0; kk < NKK / 2; ++kk) s_mfma(knext, kk, sn);
-    float mx = -INFINITY;
-#pragma unroll
-    for (int v = 0; v < 16; ++v) mx = fmaxf(mx, sc[v]);
-    mx = fmaxf(mx, other_half(mx)) * scale_log2;   // scale > 0
-    const bool upd = mx > m_ref + 8.f;                // move the reference by > 2^8 only
+    for (int v = 2; v < 8; ++v) {
+      mx = fmaxf(mx, sc[v]);
+      my = fmaxf(my, sc[8 + v]);
+    }
+    mx = fmaxf(mx, my);
+    {
+      const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx),
+                                                      false, false);
+      mx = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+    }
+    const bool upd = mx > m_thr;                      // move the reference by > 2^8 only
     if (__ballot(upd)) {
-      const float nref = upd ? mx : m_ref;
+      const float nref = upd ? mx * scale_log2 : m_ref;   // scale > 0
       const float alpha = upd ? __builtin_amdgcn_exp2f(m_ref - nref) : 1.f;
+      m_thr = upd ? mx + thr8 : m_thr;
       l_run *= alpha;
 #pragma unroll
       for (int db = 0; db < NDB; ++db)
 #pragma unroll
         for (int v = 0; v < 16; ++v) o[db][v] *= alpha;
       m_ref = nref;
+      m_neg = m_ref == -INFINITY ? 0.f : -m_ref;
     }
-    const float nref = m_ref == -INFINITY ? 0.f : -m_ref;
 #pragma unroll
     for (int hf = 0; hf < 2; ++hf) {
-      bf16x8 pg;
-      float sum = 0.f;
+      float e[8];
 #pragma unroll
-      for (int t = 0; t < 8; ++t) {
-        const float e = __builtin_amdgcn_exp2f(fmaf(sc[hf * 8 + t], scale_log2, nref));
-        sum += e;
-        pg[t] = (__bf16)e;
-      }
-      l_run += sum;
+      for (int t = 0; t < 8; ++t) e[t] = __builtin_amdgcn_exp2f(fmaf(sc[hf * 8 + t], scale_log2, m_neg));
 #pragma unroll
-      for (int db = 0; db < NDB; ++db) {
-        const unsigned char* va = vbuf + voff[db & 1] + ((16 * hf) * ROWB + 64 * (db & ~1));
-        const unsigned char* vb = vbuf + voff[db & 1] + ((16 * hf + 8) * ROWB + 64 * (db & ~1));
-        const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)va);
-        const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)vb);
-        const bf16x8 a = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-        o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, pg, o[db], 0, 0, 0);
-      }
-#pragma unroll
-      for (int kk = NKK / 2 + hf * (NKK / 4); kk < NKK / 2 + (hf + 1) * (NKK / 4); ++kk)
-        s_mfma(knext, kk, sn);
+      for (int t = 0; t < 8; ++t) pg[hf][t] = (__bf16)e[t];
+      l_run += ((e[0] + e[1]) + (e[2] + e[3])) + ((e[4] + e[5]) + (e[6] + e[7]));
     }
   };
 
-  // one step for group KG: slots of stage 2t + KG (V) and 2t + 2 + KG (K look-ahead)
-  f32x16 sA, sB;
-  auto run = [&](auto tag) __attribute__((always_inline)) {
-    constexpr int KGc = decltype(tag)::value;
-    unsigned char* const ks[8] = {s_k0, s_k1, s_k2, s_k3, s_k4, s_k5, s_k6, s_k7};
-    unsigned char* const vs[8] = {s_v0, s_v1, s_v2, s_v3, s_v4, s_v5, s_v6, s_v7};
-    int pnext1 = 0;                   // paged: the page id of this wave's next stage
-    auto step = [&](auto pt, f32x16& sc, f32x16& sn, int t) __attribute__((always_inline)) {
-      constexpr int P = decltype(pt)::value;   // t % 4
-      TAPS_WAIT_VMCNT(8);             // V(2t), V(2t+1), K(2t+2), K(2t+3): this wave's part
-      TAPS_STAGE_BARRIER();           // ... and every other wave's part; and every wave is
-                                      // done with the slots of step t - 1, refilled here
-      if constexpr (PAGED) {
-        const int qw = wave_u >> 1;                 // stage 2t + 6 + qw: V, V, K, K
-        unsigned char* const dst = qw == 0 ? vs[(2 * P + 6) & 7] : qw == 1 ? vs[(2 * P + 7) & 7]
-                                 : qw == 2 ? ks[(2 * P + 8) & 7] : ks[(2 * P + 9) & 7];
-        issue4_paged(qw < 2 ? vrs : krs, dst, 2 * t + 6 + qw,
-                     __builtin_amdgcn_readfirstlane(pnext1));
-        pnext1 = page_of_stage(2 * t + 8 + qw);      // the next step's stage of this wave
-      } else {
-        issue_at(vrs, vs[(2 * P + 6) & 7], 2 * t + 6, 0);
-        issue_at(vrs, vs[(2 * P + 7) & 7], 2 * t + 7, 0);
-        issue_at(krs, ks[(2 * P + 8) & 7], 2 * t + 8, 0);
-        issue_at(krs, ks[(2 * P + 9) & 7], 2 * t + 9, 0);
-      }
-      softmax_pv(sc, vs[(2 * P + KGc) & 7], ks[(2 * P + 2 + KGc) & 7], sn,
-                 k_begin + (2 * t + KGc) * KT);
-    };
-    TAPS_WAIT_VMCNT(4);               // K(0), K(1)
-    TAPS_LDS_BARRIER();               // every wave has its queries: V slots 4-7 refill below
-#pragma unroll
-    for (int kk = 0; kk < NKK; ++kk) s_mfma(ks[KGc], kk, sA);
-    int pg[4] = {0, 0, 0, 0};         // paged: the pages of stages 4 .. 7
+  // Phase p = 0, 1, ... of the workgroup: group kg's matrix phases are p = 2t + kg, its softmax
+  // phases p = 2t + 1 + kg.  Phase p starts with V(p) and K(p + 2) in LDS (stages of the
+  // split; its matrix group reads them) and loads V(p + 6) and K(p + 8) into the slots that
+  // phase p - 2 read: every load has six phases to arrive.
+  int pnext1 = 0;                     // paged: the page id of this wave's next stage
+  auto begin = [&](int p, bool reads_done) __attribute__((always_inline)) {
+    __builtin_amdgcn_sched_barrier(0);
+    // V(p), K(p + 2) have landed: this wave's part (paged: a wave loads four blocks in every
+    // other phase; at most its last two phases' loads stay in flight)
+    if constexpr (PAGED) TAPS_WAIT_VMCNT(8);
+    else TAPS_WAIT_VMCNT(10);
+    if (reads_done) TAPS_LDS_BARRIER();   // ... and every other wave's; a matrix phase also
+    else TAPS_STAGE_BARRIER();            // waits for the reads of this group's last one
+    const uint32_t vdst = s_v0 + ((p + 6) & 7) * TILEB, kdst = s_k0 + (p & 7) * TILEB;
     if constexpr (PAGED) {
-      read_pages4(4, pg);
-#pragma unroll
-      for (int q = 0; q < 4; ++q) pg[q] = __builtin_amdgcn_readfirstlane(pg[q]);
-      pnext1 = page_of_stage(6 + (wave_u >> 1));   // this wave's stage of the first step
+      // waves 2q and 2q + 1 load V(p + 6) (q = 0 in even phases, 1 in odd ones) or K(p + 8)
+      // (q = 2, 3), four blocks each, in every other phase
+      const int qw = wave_u >> 1;
+      if ((qw & 1) == (p & 1)) {
+        const int st = p + (qw < 2 ? 6 : 8);
+        issue4_paged(qw < 2 ? vrs : krs, qw < 2 ? vdst : kdst, st,
+                     __builtin_amdgcn_readfirstlane(pnext1));
+        pnext1 = page_of_stage(st + 2);          // this wave's next stage
+      }
+    } else {
+      issue_at(vrs, vdst, p + 6, 0);
+      issue_at(krs, kdst, p + 8, 0);
     }
-    issue(vrs, s_v2, 2); issue(vrs, s_v3, 3);
-    issue_at(krs, s_k4, 4, pg[0]); issue_at(krs, s_k5, 5, pg[1]);
-    issue_at(vrs, s_v4, 4, pg[0]); issue_at(vrs, s_v5, 5, pg[1]);
-    issue_at(krs, s_k6, 6, pg[2]); issue_at(krs, s_k7, 7, pg[3]);
-    for (int t = 0;;) {
-      step(GroupTag<0>(), sA, sB, t);
-      if (++t >= steps) break;
-      step(GroupTag<1>(), sB, sA, t);
-      if (++t >= steps) break;
-      step(GroupTag<2>(), sA, sB, t);
-      if (++t >= steps) break;
-      step(GroupTag<3>(), sB, sA, t);
-      if (++t >= steps) break;
-    }
+    __builtin_amdgcn_sched_barrier(0);
   };
-  if (kg == 0) run(GroupTag<0>());
-  else run(GroupTag<1>());
+  TAPS_WAIT_VMCNT(4);                 // K(0), K(1)
+  TAPS_LDS_BARRIER();                 // every wave has its queries: V slots 4-7 refill below
+#pragma unroll
+  for (int kk = 0; kk < NKK; ++kk) read_k(0, kk);
+  {
+    int pg4[4] = {0, 0, 0, 0};        // paged: the pages of stages 4 .. 7
+    if constexpr (PAGED) {
+      read_pages4(4, pg4);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) pg4[q] = __builtin_amdgcn_readfirstlane(pg4[q]);
+      pnext1 = page_of_stage(6 + (wave_u >> 1));   // V(6), V(7), K(8) or K(9)
+    }
+    issue(vrs, s_v0 + 2 * TILEB, 2); issue_at(krs, s_k0 + 4 * TILEB, 4, pg4[0]);
+    issue(vrs, s_v0 + 3 * TILEB, 3); issue_at(krs, s_k0 + 5 * TILEB, 5, pg4[1]);
+    issue_at(vrs, s_v0 + 4 * TILEB, 4, pg4[0]); issue_at(krs, s_k0 + 6 * TILEB, 6, pg4[2]);
+    issue_at(vrs, s_v0 + 5 * TILEB, 5, pg4[1]); issue_at(krs, s_k0 + 7 * TILEB, 7, pg4[3]);
+  }
+  if (kg == 1) begin(0, true);
+  // matrix phase of stage 2t + kg (slots of group 0; koff and voff add kg's)
+  auto mat_phase = [&](auto pt, auto first, int t) __attribute__((always_inline)) {
+    constexpr int P = 2 * decltype(pt)::value;   // 2t mod 8
+    begin(2 * t + kg, true);
+    __builtin_amdgcn_s_setprio(1);      // its MFMAs go out as soon as the matrix core is free
+#pragma unroll
+    for (int v = 0; v < 16; ++v) sc[v] = 0.f;
+#pragma unroll
+    for (int kk = 0; kk < NKK; ++kk) {
+      sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[kk], q[kk], sc, 0, 0, 0);
+      read_k((P + 2) & 7, kk);
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+    }
+#pragma unroll
+    for (int hf = 0; hf < 2; ++hf)
+#pragma unroll
+      for (int db = 0; db < NDB; ++db) {
+        if constexpr (!decltype(first)::value) {
+          o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[hf][db], pg[hf], o[db], 0, 0, 0);
+          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        }
+        read_v(P, hf, db);
+        __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+      }
+    __builtin_amdgcn_s_setprio(0);
+  };
+  auto step = [&](auto pt, int t) __attribute__((always_inline)) {
+    mat_phase(pt, GroupTag<0>(), t);
+    begin(2 * t + 1 + kg, false);
+    softmax(k_begin + (2 * t + kg) * KT);
+  };
+  mat_phase(GroupTag<0>(), GroupTag<1>(), 0);
+  begin(1 + kg, false);
+  softmax(k_begin + kg * KT);
+  for (int t = 1; t < steps; t += 4) {
+    step(GroupTag<1>(), t);
+    if (t + 1 < steps) step(GroupTag<2>(), t + 1);
+    if (t + 2 < steps) step(GroupTag<3>(), t + 2);
+    if (t + 3 < steps) step(GroupTag<0>(), t + 3);
+  }
+  __builtin_amdgcn_sched_barrier(0);
+  mul_pv();
+  if (kg == 0) TAPS_STAGE_BARRIER();  // group 1's last phase begins
   // the look-ahead loads past the split's end read nothing from memory; let them land
   // before the slots are reused and the workgroup's LDS is released
   TAPS_WAIT_VMCNT(0);
@@ -1035,28 +1094,18 @@ __device__ __attribute__((always_inline)) inline void attn_bf16_body(
   // ---- merge the key groups through LDS.  Group 0 finishes head dims 0..63 and group 1
   // dims 64..127: each wave leaves the two O^T blocks the other group finishes, and its
   // (max, sum), in the K slot of its own index.
-  auto xslot = [&](int w) -> float* {
-    switch (w) {
-      case 0: return (float*)s_k0;
-      case 1: return (float*)s_k1;
-      case 2: return (float*)s_k2;
-      case 3: return (float*)s_k3;
-      case 4: return (float*)s_k4;
-      case 5: return (float*)s_k5;
-      case 6: return (float*)s_k6;
-      default: return (float*)s_k7;
-    }
-  };
+  auto xslot = [&](int w) -> float* { return (float*)(s_k + w * TILEB); };
   {
     // 16-byte LDS accesses: value v of block j at float4 (4 j + v / 4) of this lane
     float4* mine = (float4*)xslot(wave);
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
-      const int db = kg == 0 ? 2 + j : j;     // the blocks the other group finishes
+      const f32x16 lo = o[j], hi = o[2 + j];
+      const f32x16 give = kg == 0 ? hi : lo;   // the blocks the other group finishes
 #pragma unroll
       for (int v4 = 0; v4 < 4; ++v4)
         mine[(4 * j + v4) * 64 + lane] =
-            make_float4(o[db][4 * v4], o[db][4 * v4 + 1], o[db][4 * v4 + 2], o[db][4 * v4 + 3]);
+            make_float4(give[4 * v4], give[4 * v4 + 1], give[4 * v4 + 2], give[4 * v4 + 3]);
     }
     s_ml[wave * 64 + lane] = make_float2(m_ref, lsum);
   }
@@ -1077,27 +1126,18 @@ __device__ __attribute__((always_inline)) inline void attn_bf16_body(
   // them out of the L2 leaves less to write back when the kernel ends (measured: the
   // kernel took 0.5 us less at the Qwen3-8B shape).
   constexpr int TROW = 144;            // bytes per staged row (128 + 16: fewer bank conflicts)
-  unsigned char* stage;
-  switch (wave) {
-    case 0: stage = s_v0; break;
-    case 1: stage = s_v1; break;
-    case 2: stage = s_v2; break;
-    case 3: stage = s_v3; break;
-    case 4: stage = s_v4; break;
-    case 5: stage = s_v5; break;
-    case 6: stage = s_v6; break;
-    default: stage = s_v7; break;
-  }
+  unsigned char* const stage = s_v + wave * TILEB;
 #pragma unroll
   for (int j = 0; j < 2; ++j) {
-    const int db = kg == 0 ? j : 2 + j;       // the blocks this group finishes
+    const f32x16 lo = o[j], hi = o[2 + j];
+    const f32x16 own = kg == 0 ? lo : hi;   // the blocks this group finishes
 #pragma unroll
     for (int r4 = 0; r4 < 4; ++r4) {
       const float4 th = theirs[(4 * j + r4) * 64 + lane];
       const float tv[4] = {th.x, th.y, th.z, th.w};
       float x[4];
 #pragma unroll
-      for (int t = 0; t < 4; ++t) x[t] = (o[db][4 * r4 + t] * a0 + tv[t] * a1) * inv;
+      for (int t = 0; t < 4; ++t) x[t] = (own[4 * r4 + t] * a0 + tv[t] * a1) * inv;
       *(uint2*)(stage + l32 * TROW + 2 * (j * 32 + 8 * r4 + 4 * hl)) = pack_bf16x4(x[0], x[1], x[2], x[3]);
     }
   }

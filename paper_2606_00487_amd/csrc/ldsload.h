@@ -38,18 +38,23 @@ __device__ inline i32x4 buffer_rsrc(const void* p, uint32_t bytes) {
   return r;
 }
 
-// 16 bytes per lane from buffer offset `off` straight into LDS at dst + 16 * lane, issued
+// 16 bytes per lane from buffer offset `off` straight into LDS at dst + 16 * lane (dst uniform,
+// load_lds16_at: as an LDS address in a scalar register), issued
 // as inline assembly so that the compiler does not track it.  Its own bookkeeping of
 // direct-to-LDS loads cannot tell the slots of a ring apart and would make every LDS read
 // wait for all but the newest loads in flight, which cuts the look-ahead of the ring to
 // one step.  Callers order every global read of the kernel with explicit vmcnt waits.
 // m0 carries the LDS address; nothing else in the kernels that call this uses m0.  A
 // direct-to-LDS load must not follow the scalar write of m0 immediately (one wait state).
-__device__ inline void load_lds16(const i32x4& rs, unsigned char* dst, uint32_t off) {
-  const uint32_t m0v = __builtin_amdgcn_readfirstlane(
-      (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)dst);
+__device__ inline void load_lds16_at(const i32x4& rs, uint32_t dst, uint32_t off) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
-               :: "s"(m0v), "v"(off), "s"(rs) : "memory");
+               :: "s"(dst), "v"(off), "s"(rs) : "memory");
+}
+__device__ inline uint32_t lds_address(const unsigned char* p) {
+  return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const unsigned char*)p;
+}
+__device__ inline void load_lds16(const i32x4& rs, unsigned char* dst, uint32_t off) {
+  load_lds16_at(rs, __builtin_amdgcn_readfirstlane(lds_address(dst)), off);
 }
 
 // 4 bytes per lane into LDS at dst + 4 * lane (same conventions as load_lds16)
