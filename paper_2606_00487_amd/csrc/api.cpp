@@ -80,10 +80,10 @@ struct LayerWs {
 LayerWs layer_ws(int batch, int budget, int Hq, int Hkv, int hd, int hidden, int max_ctx,
                  int page_rows = 0) {
   const int M = batch * budget, Nqkv = (Hq + 2 * Hkv) * hd;
-  const GemmPlan a = plan_gemm(M, Nqkv, hidden), o = plan_gemm(M, hidden, Hq * hd);
+  const GemmPlan a = plan_gemm(M, Nqkv, hidden, true), o = plan_gemm(M, hidden, Hq * hd, false);
   auto al = [](size_t x) { return (x + 255) & ~(size_t)255; };
   LayerWs w;
-  w.part = al(std::max((size_t)a.splits * M * Nqkv, (size_t)o.splits * M * hidden) * 4);
+  w.part = al(std::max(qkv_scratch_bytes(a, M, Nqkv), oproj_scratch_bytes(o, M, hidden)));
   w.q = al((size_t)M * Hq * hd * 2);
   w.o = w.q;
   w.attn = al(page_rows ? tree_verify_attn_paged_workspace_bytes(batch, budget, Hq, Hkv, hd,
@@ -424,17 +424,13 @@ static taps_status layer_run(const void* X, const taps_layer_weights* w, void* K
   const LayerWs L = layer_ws(batch, budget, Hq, Hkv, head_dim, hidden, max_ctx, pk ? page_rows : 0);
   if (!ws || ws_bytes < L.total || ((uintptr_t)ws & 255) != 0) return TAPS_ERR_WORKSPACE;
   const int M = batch * budget, Nq = Hq * head_dim, Nk = Hkv * head_dim;
-  float* part = (float*)ws;
+  void* part = ws;
   char* Q = (char*)ws + L.part;
   char* O = Q + L.q;
   char* aws = O + L.o;
-  const GemmPlan a = plan_gemm(M, Nq + 2 * Nk, hidden);
-  if (launch_gemm_bf16(X, M, hidden, w->Wq, Nq, w->Wk, Nk, w->Wv, Nk, a, part, stream) !=
-      hipSuccess)
-    return TAPS_ERR_HIP;
-  if (launch_qkv_rope(part, a.splits, batch, budget, Hq, Hkv, w->q_norm, w->k_norm,
-                      w->rope_theta, w->norm_eps, kv_offset, ctx_len, tree->depth,
-                      tree->n_nodes, max_ctx, Q, K_cache, V_cache, stream, pk) != hipSuccess)
+  const GemmPlan a = plan_gemm(M, Nq + 2 * Nk, hidden, true);
+  if (launch_qkv(X, hidden, *w, a, part, batch, budget, Hq, Hkv, kv_offset, ctx_len, tree->depth,
+                 tree->n_nodes, max_ctx, Q, K_cache, V_cache, stream, pk) != hipSuccess)
     return TAPS_ERR_HIP;
   if (pk) {
     const AttnPlan pl = plan_attn(batch, budget, Hq, Hkv, head_dim, max_ctx,
@@ -451,12 +447,9 @@ static taps_status layer_run(const void* X, const taps_layer_weights* w, void* K
                          stream) != hipSuccess)
       return TAPS_ERR_HIP;
   }
-  const GemmPlan o = plan_gemm(M, hidden, Nq);
-  if (launch_gemm_bf16(O, M, Nq, w->Wo, hidden, nullptr, 0, nullptr, 0, o, part, stream) !=
-      hipSuccess)
-    return TAPS_ERR_HIP;
-  return launch_reduce_bf16(part, o.splits, M, hidden, Y, stream) == hipSuccess ? TAPS_OK
-                                                                                : TAPS_ERR_HIP;
+  const GemmPlan o = plan_gemm(M, hidden, Nq, false);
+  return launch_oproj(O, M, Nq, w->Wo, hidden, o, part, Y, stream) == hipSuccess ? TAPS_OK
+                                                                                 : TAPS_ERR_HIP;
 }
 
 taps_status verify_layer(const void* X, const taps_layer_weights* w, void* K_cache,

@@ -126,23 +126,27 @@ hipError_t launch_commit(void* K, void* V, const int64_t* off, const int32_t* ct
                          int32_t* committed, int32_t* n_committed, hipStream_t s,
                          const PagedKV* pk = nullptr);
 
-// Layer slice: split-K skinny GEMM (fp32 partials [splits][M][N]), the projection
-// epilogue (RMSNorm, rotary positions, bf16 Q and cache rows) and the output reduction
+// Layer slice: the projections.  A plan with one split and a tile of more than 64 rows runs
+// its epilogue in the GEMM (Q/K/V: RMSNorm, rotary positions, bf16 Q and cache rows; output
+// projection: bf16 Y); other plans write fp32 partials [splits][M][N] that a second kernel
+// adds.
 struct GemmPlan {
-  int splits;   // K splits (partials), each a multiple of 64 K values
+  int splits;   // K splits (partials), in whole 64-value stages
   int cols;     // output columns per workgroup (64, 96 or 128)
+  int rows;     // rows per workgroup (64, 128 or 256)
+  bool fused() const { return rows > 64 && splits == 1; }
 };
-GemmPlan plan_gemm(int M, int N, int K);
-hipError_t launch_gemm_bf16(const void* X, int M, int K, const void* w0, int n0, const void* w1,
-                            int n1, const void* w2, int n2, const GemmPlan& p, float* part,
-                            hipStream_t s);
-hipError_t launch_qkv_rope(const float* part, int splits, int batch, int budget, int Hq, int Hkv,
-                           const void* q_norm, const void* k_norm, double theta, float eps,
-                           const int64_t* off, const int32_t* ctx, const int32_t* depth,
-                           const int32_t* n, int max_ctx, void* Q, void* Kc, void* Vc,
-                           hipStream_t s, const PagedKV* pk = nullptr);
-hipError_t launch_reduce_bf16(const float* part, int splits, int M, int N, void* Y,
-                              hipStream_t s);
+// head_cols: the Q/K/V projection (columns in whole heads of 128)
+GemmPlan plan_gemm(int M, int N, int K, bool head_cols);
+size_t qkv_scratch_bytes(const GemmPlan& p, int M, int N);
+size_t oproj_scratch_bytes(const GemmPlan& p, int M, int N);
+// pk != nullptr: K and V are page pools addressed through pk's block table (off unused)
+hipError_t launch_qkv(const void* X, int K, const taps_layer_weights& w, const GemmPlan& p,
+                      void* scratch, int batch, int budget, int Hq, int Hkv, const int64_t* off,
+                      const int32_t* ctx, const int32_t* depth, const int32_t* n, int max_ctx,
+                      void* Q, void* Kc, void* Vc, hipStream_t s, const PagedKV* pk = nullptr);
+hipError_t launch_oproj(const void* O, int M, int K, const void* Wo, int N, const GemmPlan& p,
+                        void* scratch, void* Y, hipStream_t s);
 
 double spec_exp_host(double t);
 

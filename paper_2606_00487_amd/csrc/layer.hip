@@ -1,22 +1,28 @@
 // One attention layer of the target over the draft tree (the layer slice of the
 // verification forward; Sec. 4.1 stage 3 and Sec. 4.3 run the target over the selected
-// tree with tree attention), bf16 storage with fp32 accumulation.  Three kernels besides
-// the tree attention of attn.hip:
+// tree with tree attention), bf16 storage with fp32 accumulation.  The kernels besides the
+// tree attention of attn.hip:
 //
 //   gemm_kernel       Y_part = X W^T for a skinny X (the budget's nodes) and a large
 //                     row-major weight [N][K]: HBM-bound on the weight, which is read once.
 //                     A workgroup owns 64, 96 or 128 output columns, 64 rows and one split
-//                     of K, planned so that the workgroups fill the 256 CUs in as few rounds
-//                     as possible (one round of exactly 256 at the Qwen3-8B shapes).  The
-//                     weight rows and X stream through a ring of LDS stages by direct loads
-//                     (~60 KB of weight in flight per CU, which HBM's latency asks for);
-//                     each of the four waves takes one 16-value k-step of every 64-value
-//                     stage on v_mfma_f32_32x32x16_bf16, and the waves' partials are added in
-//                     LDS in a fixed order.  Split partials (fp32) are added by the consumer.
+//                     of K.  The weight rows and X stream through a ring of LDS stages by
+//                     direct loads (~60 KB of weight in flight per CU, which HBM's latency
+//                     asks for); each of the four waves takes one 16-value k-step of every
+//                     64-value stage on v_mfma_f32_32x32x16_bf16, and the waves' partials are
+//                     added in LDS in a fixed order.  Split partials (fp32) are added by the
+//                     consumer.
+//   gemm_tile_kernel  the same product for many rows: tiles of 256 or 128 rows and 128
+//                     columns, each wave its own part of the tile, so a weight row is read
+//                     once per 256 rows of X instead of once per 64.  With one K split the
+//                     epilogue below runs on the accumulators and no fp32 partial is written.
 //   qkv_rope_kernel   adds the projection's split partials, applies the per-head RMSNorm
 //                     and the rotary embedding at position ctx + depth, and stores Q and the
 //                     cache rows ctx + i of K and V in bf16.
+//   rotation_kernel   the rotations for the fused epilogue.
 //   reduce_kernel     adds the output projection's split partials and rounds to bf16.
+#include <algorithm>
+
 #include "common.h"
 #include "ldsload.h"
 
@@ -82,7 +88,9 @@ __global__ __launch_bounds__(256) void gemm_kernel(const uint16_t* __restrict__ 
   const int tid = threadIdx.x, lane = tid & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
   const int l32 = lane & 31, hl = lane >> 5;
-  const int Ks = K / splits, S = Ks / 64, kb = split * Ks;
+  // this split's stages: sb .. sb + S - 1 (the split count is a power of two)
+  const int S0 = K / 64, lg = __builtin_ctz((unsigned)splits), sb = (S0 * split) >> lg;
+  const int S = ((S0 * (split + 1)) >> lg) - sb, kb = sb * 64;
   const uint32_t rowb = (uint32_t)K * 2;
   const int mrows = min(64, M - m0);
 
@@ -328,46 +336,376 @@ __global__ __launch_bounds__(256) void reduce_kernel(const float* __restrict__ p
   *(uint2*)(Y + e) = o;
 }
 
-}  // namespace
+// Y = X W^T for many rows: a tile of 128 TM rows and 128 output columns over one split of K per
+// workgroup of 4 x 2 waves, each wave TM x 2 blocks of v_mfma_f32_32x32x16_bf16.  X rows and
+// weight rows stream through a ring of D LDS stages of 64 values of K by direct loads, 128-byte
+// rows with their chunks permuted by row_swz as in gemm_kernel.  The weight is the A operand, so
+// a lane ends with runs of four consecutive columns of one row; wave column wn takes the column
+// blocks wn and wn + 2, so a lane holds both values of every rotary pair (d, d + 64) of its head.
+//   EP = kPartial: fp32 partials [split][M][N];  kBf16: one split, Y in bf16;
+//   kRope, kRopePaged: one split of the Q/K/V projection: RMSNorm, rotation and the stores of
+//   qkv_rope_kernel, from the accumulators (the tile is one head's 128 columns).
+// Bound: a stage of 256 rows is 1024 clocks of matrix instructions per SIMD and 48 KB of
+// direct loads, which the CU takes at 54 B/clk at most (a microbenchmark on cached rows), about
+// 900 clocks.  2048 x 4096 x 6144 takes ~110 us (0.94 PFLOP/s) and 2048 x 4096 x 4096 60 us (1.14
+// PFLOP/s; one exact round), against 180 + 32 (qkv_rope_kernel) and 119 + 9 us (reduce_kernel)
+// with 64-row tiles.
+enum { kPartial = 0, kBf16 = 1, kRope = 2, kRopePaged = 3 };
 
-GemmPlan plan_gemm(int M, int N, int K) {
-  // Candidates (64, 96 or 128 columns per workgroup; K splits 1 .. 16)
-  // are ranked by how full their last round of workgroups leaves the 256 CUs (one
-  // workgroup per CU: the ring takes most of the LDS), then by fewer rounds, then by fewer
-  // splits (less partial traffic).  N is a multiple of 64 and K of 64, so 64 columns and
-  // one split always qualify.
-  const long long mt = (M + 63) / 64;
-  GemmPlan best{1, 64};
-  double best_fill = -1.0;
-  long long best_rounds = 0;
-  for (int nb = 2; nb <= 4; ++nb) {
-    if (N % (32 * nb) != 0) continue;
-    for (int sp = 1; sp <= 16 && K % (64 * sp) == 0; sp *= 2) {
-      const long long wgs = (long long)(N / (32 * nb)) * sp * mt;
-      const long long rounds = (wgs + 255) / 256;
-      const double fill = (double)wgs / (double)(rounds * 256);
-      const bool better =
-          fill > best_fill + 1e-9 ||
-          (fill > best_fill - 1e-9 &&
-           (rounds < best_rounds || (rounds == best_rounds && sp < best.splits)));
-      if (better) {
-        best = GemmPlan{sp, 32 * nb};
-        best_fill = fill;
-        best_rounds = rounds;
+struct RopeOut {
+  const uint16_t *q_norm, *k_norm;
+  const float2* rot;          // [M][64] (cos, sin) of every node's pairs
+  const int64_t* off;
+  const int32_t *ctx, *n;
+  uint16_t *Q, *K, *V;
+  PagedKV pk;
+  float eps;
+  int max_ctx, budget, Hq, Hkv;
+};
+
+__device__ inline uint2 pack4(float a, float b, float c, float d) {
+  return make_uint2((uint32_t)f32_to_bf16(a) | ((uint32_t)f32_to_bf16(b) << 16),
+                    (uint32_t)f32_to_bf16(c) | ((uint32_t)f32_to_bf16(d) << 16));
+}
+
+constexpr int kTileRing = 3 * (128 + 256) * 128;   // LDS bytes of either tile height's ring
+
+// One tile of 128 TM rows from row m0 and 128 columns from column c0, K split `split`
+template <int TM, int D, int EP>
+__device__ __attribute__((always_inline)) inline void gemm_tile(
+    const uint16_t* __restrict__ X, int M, int K, const WSeg& ws, int N, int splits, int split,
+    int m0, int c0, void* __restrict__ out, const RopeOut& ro, unsigned char* s_ring) {
+  constexpr int WM = 4, WN = 2, TN = 2, NW = WM * WN;
+  constexpr int BM = 32 * WM * TM, BN = 32 * WN * TN;
+  constexpr int WSLOT = BN * 128, XSLOT = BM * 128;
+  constexpr int WL = BN / 8 / NW, XL = BM / 8 / NW;   // direct loads per wave and stage
+  constexpr int PER = WL + XL;
+  static_assert(D * (WSLOT + XSLOT) <= kTileRing, "the ring fits");
+  static_assert((D - 1) * PER <= 63, "vmcnt counts at most 63 operations");
+  const int tid = threadIdx.x, lane = tid & (kWave - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+  const int wm = wave / WN, wn = wave % WN;
+  const int l32 = lane & 31, hl = lane >> 5;
+  // this split's stages: sb .. sb + S - 1 (the split count is a power of two)
+  const int S0 = K / 64, lg = __builtin_ctz((unsigned)splits), sb = (S0 * split) >> lg;
+  const int S = ((S0 * (split + 1)) >> lg) - sb, kb = sb * 64;
+  const uint32_t rowb = (uint32_t)K * 2;
+  const int mrows = min(BM, M - m0), ncols = min(BN, N - c0);
+
+  // wave-load g of an operand fills 1 KB = 8 rows of its slot (rows past the end repeat the
+  // last); the tile's weight rows lie in one of the weight arrays
+  const uint16_t* wrow = c0 < ws.end0   ? ws.w0 + (size_t)c0 * K
+                         : c0 < ws.end1 ? ws.w1 + (size_t)(c0 - ws.end0) * K
+                                        : ws.w2 + (size_t)(c0 - ws.end1) * K;
+  const i32x4 wrs = buffer_rsrc(wrow, (uint32_t)ncols * rowb);
+  const i32x4 xrs = buffer_rsrc(X + (size_t)m0 * K, (uint32_t)mrows * rowb);
+  uint32_t woff[WL], xoff[XL];
+#pragma unroll
+  for (int j = 0; j < WL; ++j) {
+    const int r = 8 * (WL * wave + j) + (lane >> 3);
+    woff[j] = (uint32_t)min(r, ncols - 1) * rowb + (uint32_t)(kb + 8 * ((lane & 7) ^ row_swz(r))) * 2u;
+  }
+#pragma unroll
+  for (int j = 0; j < XL; ++j) {
+    const int r = 8 * (XL * wave + j) + (lane >> 3);
+    xoff[j] = (uint32_t)min(r, mrows - 1) * rowb + (uint32_t)(kb + 8 * ((lane & 7) ^ row_swz(r))) * 2u;
+  }
+  auto issue = [&](int slot, int st) __attribute__((always_inline)) {
+    unsigned char* sw = s_ring + slot * WSLOT;
+    unsigned char* sx = s_ring + D * WSLOT + slot * XSLOT;
+#pragma unroll
+    for (int j = 0; j < WL; ++j)
+      load_lds16(wrs, sw + (WL * wave + j) * 1024, woff[j] + (uint32_t)st * 128u);
+#pragma unroll
+    for (int j = 0; j < XL; ++j)
+      load_lds16(xrs, sx + (XL * wave + j) * 1024, xoff[j] + (uint32_t)st * 128u);
+  };
+
+  f32x16 acc[TN][TM];
+#pragma unroll
+  for (int c = 0; c < TN; ++c)
+#pragma unroll
+    for (int r = 0; r < TM; ++r)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[c][r][v] = 0.f;
+  // operands of the 16-value k-step kk of a stage
+  const int rsw = row_swz(l32);
+  bf16x8 xa[4][TM], wb[4][TN];
+  auto read = [&](int slot, int kk) __attribute__((always_inline)) {
+    const int ch = 16 * ((2 * kk + hl) ^ rsw);
+    const unsigned char* sw = s_ring + slot * WSLOT + (wn * 32 + l32) * 128 + ch;
+    const unsigned char* sx = s_ring + D * WSLOT + slot * XSLOT + (wm * TM * 32 + l32) * 128 + ch;
+#pragma unroll
+    for (int c = 0; c < TN; ++c) wb[kk][c] = *(const bf16x8*)(sw + c * WN * 32 * 128);
+#pragma unroll
+    for (int r = 0; r < TM; ++r) xa[kk][r] = *(const bf16x8*)(sx + r * 32 * 128);
+  };
+  auto multiply = [&](int kk) __attribute__((always_inline)) {
+#pragma unroll
+    for (int c = 0; c < TN; ++c)
+#pragma unroll
+      for (int r = 0; r < TM; ++r)
+        acc[c][r] =
+            __builtin_amdgcn_mfma_f32_32x32x16_bf16(wb[kk][c], xa[kk][r], acc[c][r], 0, 0, 0);
+  };
+
+  // A wave holds the operands of a whole stage and reads those of the next one right behind
+  // the products that used them.  At stage s it has waited for its loads of stage s + 1 and
+  // met the others, whose operands of stage s have arrived too: slot s % D takes stage s + D.
+  for (int s = 0; s < D && s < S; ++s) issue(s, s);
+  if (S >= D) TAPS_WAIT_VMCNT((D - 1) * PER);
+  else TAPS_WAIT_VMCNT(0);
+  TAPS_STAGE_BARRIER();
+#pragma unroll
+  for (int kk = 0; kk < 4; ++kk) read(0, kk);
+  for (int s0 = 0; s0 < S; s0 += D) {
+#pragma unroll
+    for (int i = 0; i < D; ++i) {
+      const int s = s0 + i;
+      if (s + 1 < S) {   // uniform
+        if (s + D - 1 < S) TAPS_WAIT_VMCNT((D - 2) * PER);   // stage s + 1 landed
+        else TAPS_WAIT_VMCNT(0);
+        TAPS_LDS_BARRIER();
+        if (s + D < S) issue(i, s + D);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk) {
+          multiply(kk);
+          __builtin_amdgcn_sched_group_barrier(0x008, TM * TN, 0);
+          read((i + 1) % D, kk);
+          __builtin_amdgcn_sched_group_barrier(0x100, TM + TN, 0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
       }
     }
+  }
+#pragma unroll
+  for (int kk = 0; kk < 4; ++kk) multiply(kk);   // the last stage
+
+  // accumulator element v of lane (l32, hl): row l32 of its row block, column
+  // 8 (v / 4) + 4 hl + v % 4 of its column block
+  if constexpr (EP == kPartial || EP == kBf16) {
+#pragma unroll
+    for (int r = 0; r < TM; ++r) {
+      const int row = m0 + (wm * TM + r) * 32 + l32;
+      if (row >= M) continue;
+#pragma unroll
+      for (int c = 0; c < TN; ++c) {
+        const int cb = c0 + 32 * (wn + WN * c);
+        if (cb >= N) continue;   // N is a multiple of 64: whole column blocks
+#pragma unroll
+        for (int v4 = 0; v4 < 4; ++v4) {
+          const int col = cb + 8 * v4 + 4 * hl;
+          const f32x16& a = acc[c][r];
+          if constexpr (EP == kPartial)
+            *(float4*)((float*)out + ((size_t)split * M + row) * N + col) =
+                make_float4(a[4 * v4], a[4 * v4 + 1], a[4 * v4 + 2], a[4 * v4 + 3]);
+          else
+            *(uint2*)((uint16_t*)out + (size_t)row * N + col) =
+                pack4(a[4 * v4], a[4 * v4 + 1], a[4 * v4 + 2], a[4 * v4 + 3]);
+        }
+      }
+    }
+  } else {
+    constexpr int HD = 128;
+    const int h = c0 / HD, Hq = ro.Hq, Hkv = ro.Hkv;
+    const bool value = h >= Hq + Hkv;
+    float* s_ss = (float*)s_ring;   // [wn][BM] partial sums of squares
+    __syncthreads();                // every wave is done with the ring
+    if (!value) {
+#pragma unroll
+      for (int r = 0; r < TM; ++r) {
+        float ss = 0.f;
+#pragma unroll
+        for (int c = 0; c < TN; ++c)
+#pragma unroll
+          for (int v = 0; v < 16; ++v) ss += acc[c][r][v] * acc[c][r][v];
+        ss += __shfl_xor(ss, 32);
+        if (hl == 0) s_ss[wn * BM + (wm * TM + r) * 32 + l32] = ss;
+      }
+      __syncthreads();
+    }
+    const uint16_t* nw = h < Hq ? ro.q_norm : ro.k_norm;
+#pragma unroll
+    for (int r = 0; r < TM; ++r) {
+      const int lr = (wm * TM + r) * 32 + l32, row = m0 + lr;
+      if (row >= M) continue;
+      const int b = row / ro.budget, i = row - b * ro.budget;
+      if (i >= min(max(ro.n[b], 0), ro.budget)) continue;
+      uint16_t* dst;
+      if (h < Hq) {
+        dst = ro.Q + ((size_t)row * Hq + h) * HD;
+      } else {
+        const int L = min(max(ro.ctx[b], 0), ro.max_ctx) + i;
+        size_t crow;
+        if constexpr (EP == kRopePaged) {
+          const PagedKV& pk = ro.pk;
+          int pg = pk.btab[(size_t)b * pk.max_pages + min(L >> pk.page_shift, pk.max_pages - 1)];
+          pg = min(max(pg, 0), pk.num_pages - 1);
+          crow = (((size_t)pg << pk.page_shift) | (size_t)(L & ((1 << pk.page_shift) - 1)));
+        } else {
+          crow = (size_t)(ro.off[b] + L);
+        }
+        dst = value ? ro.V + (crow * Hkv + (h - Hq - Hkv)) * HD : ro.K + (crow * Hkv + (h - Hq)) * HD;
+      }
+      float inv = 1.f;
+      if (!value) {
+        const float ss = s_ss[lr] + s_ss[BM + lr];
+        inv = 1.0f / sqrtf(ss * (1.0f / HD) + ro.eps);
+      }
+#pragma unroll
+      for (int v4 = 0; v4 < 4; ++v4) {
+        const int d = 32 * wn + 8 * v4 + 4 * hl;   // and d + 64
+        float z0[4], z1[4];
+        if (value) {
+#pragma unroll
+          for (int t = 0; t < 4; ++t) {
+            z0[t] = acc[0][r][4 * v4 + t];
+            z1[t] = acc[1][r][4 * v4 + t];
+          }
+        } else {
+#pragma unroll
+          for (int t = 0; t < 4; ++t) {
+            const float2 cs2 = ro.rot[(size_t)row * (HD / 2) + d + t];
+            const float y0 = acc[0][r][4 * v4 + t] * inv * bf16_to_f32(nw[d + t]);
+            const float y1 = acc[1][r][4 * v4 + t] * inv * bf16_to_f32(nw[d + t + 64]);
+            z0[t] = y0 * cs2.x - y1 * cs2.y;
+            z1[t] = y1 * cs2.x + y0 * cs2.y;
+          }
+        }
+        *(uint2*)(dst + d) = pack4(z0[0], z0[1], z0[2], z0[3]);
+        *(uint2*)(dst + d + 64) = pack4(z1[0], z1[1], z1[2], z1[3]);
+      }
+    }
+  }
+}
+
+// The tiles, row tiles fastest, then splits, then columns: the first `full` of 256 rows, the
+// others as two tiles of 128 rows each.  Every XCD takes a run of consecutive tiles, so its L2
+// holds the weight rows of a few column tiles at a time.
+template <int EP>
+__global__ __launch_bounds__(512) void gemm_tile_kernel(const uint16_t* __restrict__ X, int M,
+                                                        int K, WSeg ws, int N, int splits,
+                                                        int rtiles, int tiles, int full,
+                                                        void* __restrict__ out, RopeOut ro) {
+  __shared__ __attribute__((aligned(16))) unsigned char s_ring[kTileRing];
+  const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
+  const int fper = (full + 7) >> 3;
+  auto where = [&](int tile, int& split, int& m0, int& c0) {
+    const int cs = tile / rtiles, ct = cs / splits;
+    m0 = (tile - cs * rtiles) * 256;
+    split = cs - ct * splits;
+    c0 = ct * 128;
+  };
+  int split, m0, c0;
+  if (slot < fper) {
+    const int tile = xcd * fper + slot;
+    if (tile >= full) return;
+    where(tile, split, m0, c0);
+    gemm_tile<2, 3, EP>(X, M, K, ws, N, splits, split, m0, c0, out, ro, s_ring);
+  } else {
+    const int halves = 2 * (tiles - full), hper = (halves + 7) >> 3;
+    const int h = xcd * hper + slot - fper;
+    if (slot - fper >= hper || h >= halves) return;
+    where(full + (h >> 1), split, m0, c0);
+    m0 += 128 * (h & 1);
+    if (m0 >= M) return;
+    gemm_tile<1, 4, EP>(X, M, K, ws, N, splits, split, m0, c0, out, ro, s_ring);
+  }
+}
+
+// Rotations of every node at position ctx + depth, from fp64 angles, for the fused epilogue:
+// one wave per kRotRows nodes, lane j the pair (j, j + 64).
+constexpr int kRotRows = 2;
+__global__ __launch_bounds__(256) void rotation_kernel(int M, int budget, double theta,
+                                                       const int32_t* __restrict__ ctxp,
+                                                       const int32_t* __restrict__ depthp,
+                                                       int max_ctx, float2* __restrict__ rot) {
+  const int lane = threadIdx.x & (kWave - 1);
+  const int r0 = (blockIdx.x * 4 + threadIdx.x / kWave) * kRotRows;
+  int pos[kRotRows];
+#pragma unroll
+  for (int k = 0; k < kRotRows; ++k) {
+    const int row = min(r0 + k, M - 1);
+    pos[k] = min(max(ctxp[row / budget], 0), max_ctx) + max(depthp[row], 0);
+  }
+  const double f = pow(theta, -2.0 * (double)lane / 128.0);
+#pragma unroll
+  for (int k = 0; k < kRotRows; ++k) {
+    double sd, cd;
+    sincos((double)pos[k] * f, &sd, &cd);
+    if (r0 + k < M) rot[(size_t)(r0 + k) * 64 + lane] = make_float2((float)cd, (float)sd);
+  }
+}
+
+}  // namespace
+
+struct TileGrid {
+  int rtiles, tiles, full, blocks;
+};
+// Whole rounds of 256 workgroups (one per CU) take 256-row tiles; what is left takes them too
+// unless its 128-row tiles fit one round.
+static TileGrid tile_grid(int M, int N, int splits) {
+  TileGrid g;
+  g.rtiles = (M + 255) / 256;
+  g.tiles = g.rtiles * splits * ((N + 127) / 128);
+  const int rest = g.tiles % 256;
+  const long long halves = (long long)rest * ((M + 127) / 128) / g.rtiles;   // with rows
+  g.full = halves <= 256 ? g.tiles - rest : g.tiles;
+  g.blocks = 8 * ((g.full + 7) / 8 + (2 * (g.tiles - g.full) + 7) / 8);
+  return g;
+}
+
+// The candidate with the least estimated time, in microseconds, from these measurements: a
+// round of 256 workgroups (one per CU: the rings take most of the LDS) takes per 64-value stage
+// 0.30, 0.37 or 0.42 in the 64-row kernel of 64, 96 or 128 columns, 0.94 for tiles of 256 rows
+// and 0.70 for tiles of 128, plus 3 to 4 for its start and end; a CU streams weights from HBM
+// at 19.5 KB/us (the row tiles of a column share them); fp32 partials are written and read at
+// 4 TB/s and cost a launch of 4 more; the fused Q/K/V epilogue costs the rotations' launch.
+// For 11 layer shapes from 33 to 2048 rows the choice was within 3 us of the best candidate.
+GemmPlan plan_gemm(int M, int N, int K, bool head_cols) {
+  const int S0 = K / 64;
+  GemmPlan best{1, 64, 64};
+  double best_us = -1.0;
+  auto consider = [&](const GemmPlan& p, double us) {
+    if (!p.fused()) us += 8.0 * p.splits * M * N / 4.0e6 + 4.0;
+    else if (head_cols) us += 4.5;
+    if (best_us < 0.0 || us < best_us) {
+      best = p;
+      best_us = us;
+    }
+  };
+  for (int sp = 1; sp <= 16 && sp <= S0; sp *= 2) {
+    const int S = (S0 + sp - 1) / sp;
+    for (int nb = 2; nb <= 4; ++nb) {
+      if (N % (32 * nb) != 0) continue;   // N is a multiple of 64: 64 columns always qualify
+      const long long wgs = (long long)(N / (32 * nb)) * sp * ((M + 63) / 64);
+      const double stage = std::max(nb == 2 ? 0.30 : nb == 3 ? 0.37 : 0.42,
+                                    0.21 * nb / (double)((M + 63) / 64));
+      consider(GemmPlan{sp, 32 * nb, 64}, (double)((wgs + 255) / 256) * (S * stage + 3.0));
+    }
+    const TileGrid g = tile_grid(M, N, sp);
+    const double half = std::max(0.70, 0.84 / (double)((M + 127) / 128));
+    consider(GemmPlan{sp, 128, 256}, (double)((g.full + 255) / 256) * (S * 0.94 + 4.0) +
+                                         (g.full < g.tiles ? S * half + 4.0 : 0.0));
   }
   return best;
 }
 
-hipError_t launch_gemm_bf16(const void* X, int M, int K, const void* w0, int n0, const void* w1,
-                            int n1, const void* w2, int n2, const GemmPlan& p, float* part,
-                            hipStream_t s) {
-  const WSeg ws{(const uint16_t*)w0, (const uint16_t*)w1, (const uint16_t*)w2, n0, n0 + n1};
-  const int N = n0 + n1 + n2;
-  if (M <= 0) return hipSuccess;
+// fp32 partials of X W^T (p.splits of them), or with EP the fused outputs
+template <int EP>
+static hipError_t launch_tile(const uint16_t* x, int M, int K, const WSeg& ws, int N,
+                              const GemmPlan& p, void* out, const RopeOut& ro, hipStream_t s) {
+  const TileGrid g = tile_grid(M, N, p.splits);
+  gemm_tile_kernel<EP><<<(unsigned)g.blocks, 512, 0, s>>>(x, M, K, ws, N, p.splits, g.rtiles,
+                                                          g.tiles, g.full, out, ro);
+  return hipGetLastError();
+}
+
+static hipError_t launch_partials(const uint16_t* x, int M, int K, const WSeg& ws, int N,
+                                  const GemmPlan& p, float* part, hipStream_t s) {
+  if (p.rows > 64) return launch_tile<kPartial>(x, M, K, ws, N, p, part, RopeOut{}, s);
   const dim3 grid((unsigned)(N / p.cols), (unsigned)p.splits, (unsigned)((M + 63) / 64));
-  const uint16_t* x = (const uint16_t*)X;
   switch (p.cols) {   // ring depth: 120-144 KB of LDS
     case 64: gemm_kernel<2, 8><<<grid, 256, 0, s>>>(x, M, K, ws, N, p.splits, part); break;
     case 96: gemm_kernel<3, 6><<<grid, 256, 0, s>>>(x, M, K, ws, N, p.splits, part); break;
@@ -377,12 +715,11 @@ hipError_t launch_gemm_bf16(const void* X, int M, int K, const void* w0, int n0,
   return hipGetLastError();
 }
 
-hipError_t launch_qkv_rope(const float* part, int splits, int batch, int budget, int Hq, int Hkv,
-                           const void* q_norm, const void* k_norm, double theta, float eps,
-                           const int64_t* off, const int32_t* ctx, const int32_t* depth,
-                           const int32_t* n, int max_ctx, void* Q, void* Kc, void* Vc,
-                           hipStream_t s, const PagedKV* pk) {
-
+static hipError_t launch_qkv_rope(const float* part, int splits, int batch, int budget, int Hq,
+                                  int Hkv, const void* q_norm, const void* k_norm, double theta,
+                                  float eps, const int64_t* off, const int32_t* ctx,
+                                  const int32_t* depth, const int32_t* n, int max_ctx, void* Q,
+                                  void* Kc, void* Vc, hipStream_t s, const PagedKV* pk) {
   const int M = batch * budget, H = Hq + 2 * Hkv;
   // four heads per wave once there are many (node, head) pairs: the fp64 rotation is then
   // computed once per four heads, and the grid still holds thousands of waves
@@ -416,7 +753,7 @@ hipError_t launch_qkv_rope(const float* part, int splits, int batch, int budget,
   return hipGetLastError();
 }
 
-hipError_t launch_reduce_bf16(const float* part, int splits, int M, int N, void* Y,
+static hipError_t launch_reduce_bf16(const float* part, int splits, int M, int N, void* Y,
                               hipStream_t s) {
   const size_t total = (size_t)M * N;     // a multiple of 4 (N is a multiple of 64)
   const unsigned blocks = (unsigned)((total / 4 + 255) / 256);
@@ -429,6 +766,51 @@ hipError_t launch_reduce_bf16(const float* part, int splits, int M, int N, void*
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
+}
+
+size_t qkv_scratch_bytes(const GemmPlan& p, int M, int N) {
+  return p.fused() ? (size_t)M * 64 * sizeof(float2) : (size_t)p.splits * M * N * sizeof(float);
+}
+size_t oproj_scratch_bytes(const GemmPlan& p, int M, int N) {
+  return p.fused() ? 0 : (size_t)p.splits * M * N * sizeof(float);
+}
+
+hipError_t launch_qkv(const void* X, int K, const taps_layer_weights& w, const GemmPlan& p,
+                      void* scratch, int batch, int budget, int Hq, int Hkv, const int64_t* off,
+                      const int32_t* ctx, const int32_t* depth, const int32_t* n, int max_ctx,
+                      void* Q, void* Kc, void* Vc, hipStream_t s, const PagedKV* pk) {
+  const int M = batch * budget, nq = Hq * 128, nk = Hkv * 128, N = nq + 2 * nk;
+  if (M <= 0) return hipSuccess;
+  const uint16_t* x = (const uint16_t*)X;
+  const WSeg ws{(const uint16_t*)w.Wq, (const uint16_t*)w.Wk, (const uint16_t*)w.Wv, nq, nq + nk};
+  if (!p.fused()) {
+    const hipError_t e = launch_partials(x, M, K, ws, N, p, (float*)scratch, s);
+    if (e != hipSuccess) return e;
+    return launch_qkv_rope((const float*)scratch, p.splits, batch, budget, Hq, Hkv, w.q_norm,
+                           w.k_norm, w.rope_theta, w.norm_eps, off, ctx, depth, n, max_ctx, Q, Kc,
+                           Vc, s, pk);
+  }
+  float2* rot = (float2*)scratch;
+  rotation_kernel<<<(unsigned)((M + 4 * kRotRows - 1) / (4 * kRotRows)), 256, 0, s>>>(
+      M, budget, w.rope_theta, ctx, depth, max_ctx, rot);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  const RopeOut ro{(const uint16_t*)w.q_norm, (const uint16_t*)w.k_norm, rot, off, ctx, n,
+                   (uint16_t*)Q, (uint16_t*)Kc, (uint16_t*)Vc,
+                   pk ? *pk : PagedKV{nullptr, 0, 1, 5}, w.norm_eps, max_ctx, budget, Hq, Hkv};
+  return pk ? launch_tile<kRopePaged>(x, M, K, ws, N, p, nullptr, ro, s)
+            : launch_tile<kRope>(x, M, K, ws, N, p, nullptr, ro, s);
+}
+
+hipError_t launch_oproj(const void* O, int M, int K, const void* Wo, int N, const GemmPlan& p,
+                        void* scratch, void* Y, hipStream_t s) {
+  if (M <= 0) return hipSuccess;
+  const uint16_t* x = (const uint16_t*)O;
+  const WSeg ws{(const uint16_t*)Wo, nullptr, nullptr, N, N};
+  if (p.fused()) return launch_tile<kBf16>(x, M, K, ws, N, p, Y, RopeOut{}, s);
+  const hipError_t e = launch_partials(x, M, K, ws, N, p, (float*)scratch, s);
+  if (e != hipSuccess) return e;
+  return launch_reduce_bf16((const float*)scratch, p.splits, M, N, Y, s);
 }
 
 }  // namespace taps
