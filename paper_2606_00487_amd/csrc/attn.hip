@@ -108,6 +108,140 @@ typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
 // at once, land on distinct LDS banks
 __device__ inline int kswz(int r) { return ((r & 3) << 1) | ((r >> 2) & 1); }
 
+// inclusive prefix sum over the lanes of a wave (DPP row shifts, then row broadcasts)
+__device__ inline int wave_inclusive_sum(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);  // row_shr:1
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);  // row_shr:2
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);  // row_shr:4
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);  // row_shr:8
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);  // row_bcast:15
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);  // row_bcast:31
+  return v;
+}
+
+// sum of a 64-bit integer over the lanes of a wave, in every lane
+__device__ inline long long wave_sum_i64(long long v) {
+#pragma unroll
+  for (int m = 32; m >= 1; m >>= 1) {
+    const uint32_t lo = __shfl_xor((uint32_t)v, m), hi = __shfl_xor((uint32_t)((uint64_t)v >> 32), m);
+    v += (long long)(((uint64_t)hi << 32) | lo);
+  }
+  return v;
+}
+
+// maximum of non-negative ints over the lanes of a wave, as a uniform value (DPP, no LDS
+// round trips: a workgroup issues no load before its pick is made)
+__device__ inline int wave_max_nonneg(int v) {
+  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false));
+  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false));
+  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false));
+  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false));
+  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false));
+  v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false));
+  return __builtin_amdgcn_readlane(v, 63);
+}
+
+// Ragged work list of several requests.  Request b has R_b keys (context rows + nodes) and
+// S_b = ceil(R_b / L) splits per KV head; its pairs are numbered from the prefix sum E_b of
+// Hkv * S_b, KV head by KV head.  When the lengths are close (the longest at most 5/4 of
+// the mean), L is the host's split length for max_ctx + budget keys, as in the one-request
+// plan.  Otherwise L is the one of 64 candidate lengths (one per lane, sized for 1/64 ..
+// 64/64 of target_pairs pairs) with the least estimated time for the batch's actual
+// lengths, or for more than 64 requests the one sized for 3/4 of target_pairs.  Every wave
+// of the workgroup computes the same result; wave 0 of the designated workgroup also writes
+// tab[b] = (E_b, S_b) and tab[batch] = (L, total pairs) for the split combine.
+//
+// The estimate, in 64-key steps, with `resident` workgroups at a time and `fixed` steps'
+// worth of prologue and partial writes in each: one workgroup takes L / 64 + fixed; a list
+// that fits the chip takes that long, a longer one the lesser of its full rounds and of the
+// mean load plus half a workgroup (the lists end in splits of all lengths).
+struct RaggedCost {
+  int resident, fixed;
+};
+struct RaggedPick {
+  int b, g, split, L;
+  bool found;
+};
+__device__ inline RaggedPick ragged_pick(const int32_t* ctxp, const int32_t* nnp, int batch,
+                                         int N, int max_ctx, int Hkv, int mtiles,
+                                         int target_pairs, RaggedCost rc, int lcap, int L_host,
+                                         int p, int2* tab, bool write_tab) {
+  const int lane = threadIdx.x & 63;
+  long long tot = 0;
+  int rmax = 0, r_first = 0;
+  for (int c = 0; c < batch; c += 64) {
+    const int b = c + lane;
+    if (b < batch) {
+      const int R = min(max(ctxp[b], 0), max_ctx) + min(max(nnp[b], 0), N);
+      tot += R;
+      rmax = max(rmax, R);
+      if (c == 0) r_first = R;
+    }
+  }
+  if (batch <= 64) {   // one request per lane: two 32-bit sums hold the total
+    const int lo = __builtin_amdgcn_readlane(wave_inclusive_sum(r_first & 0xFFFF), 63);
+    const int hi = __builtin_amdgcn_readlane(wave_inclusive_sum(r_first >> 16), 63);
+    tot = ((long long)hi << 16) + lo;
+  } else {
+    tot = wave_sum_i64(tot);
+  }
+  rmax = wave_max_nonneg(rmax);
+  int L;
+  if (4ll * rmax * batch <= 5ll * tot) {
+    L = L_host;
+  } else {
+    // the candidate's length: at least the exact quotient up to fp32 rounding, which adds
+    // less than one pair in target_pairs, so the pair count stays within target_pairs +
+    // batch * Hkv
+    const int T = batch > 64 ? max(1, target_pairs * 3 / 4) : max(1, (target_pairs * (lane + 1)) >> 6);
+    const float keys = (float)(tot * Hkv);
+    const float want = fminf(ceilf(keys / (float)T), (float)lcap);
+    L = min(lcap, max(128, ((int)want + 63) / 64 * 64));
+    if (batch <= 64) {   // uniform
+      const float inv = 1.f / (float)L;
+      float s = 0.f;
+      for (int b = 0; b < batch; ++b)
+        s += ceilf((float)__builtin_amdgcn_readlane(r_first, b) * inv - 1e-4f);
+      const float wgs = s * (float)(Hkv * mtiles), res = (float)rc.resident;
+      const float one = (float)(L / 64 + rc.fixed);
+      const float mean = (keys * (float)mtiles * (1.f / 64.f) + wgs * (float)rc.fixed) / res;
+      const float cost =
+          wgs <= res ? one : fminf(ceilf(wgs / res) * one, mean + 0.5f * one);
+      // the least cost: positive floats order like their bits
+      const int key = 0x7FFFFFFF - (int)__float_as_uint(cost);
+      L = __builtin_amdgcn_readlane(L, __ffsll((long long)__ballot(key == wave_max_nonneg(key))) - 1);
+    }
+  }
+  RaggedPick r;
+  r.b = r.g = r.split = 0;
+  r.L = L;
+  r.found = false;
+  int carry = 0;
+  for (int c = 0; c < batch; c += 64) {
+    const int b = c + lane;
+    int R = 0;
+    if (b < batch) R = min(max(ctxp[b], 0), max_ctx) + min(max(nnp[b], 0), N);
+    const int S = (R + L - 1) / L;
+    const int P = Hkv * S;
+    const int incl = carry + wave_inclusive_sum(P);
+    const int excl = incl - P;
+    if (write_tab && b < batch) tab[b] = make_int2(excl, S);
+    const uint64_t m = __ballot(b < batch && P > 0 && excl <= p && p < incl);
+    if (m && !r.found) {
+      const int l = __ffsll((long long)m) - 1;
+      const int local = p - __builtin_amdgcn_readlane(excl, l);
+      const int Sb = __builtin_amdgcn_readlane(S, l);
+      r.b = c + l;
+      r.g = local / Sb;
+      r.split = local - r.g * Sb;
+      r.found = true;
+    }
+    carry = __builtin_amdgcn_readlane(incl, 63);
+  }
+  if (write_tab && lane == 0) tab[batch] = make_int2(L, carry);
+  return r;
+}
+
 // One workgroup: four waves, 32 query rows each (S^T and O^T tiles of one 32x32 MFMA
 // block per 32 keys and per 32 head dimensions), one 64-key stage of K and V per step.
 // K and V tiles go from global memory straight into LDS with buffer loads (16 bytes per
@@ -131,7 +265,8 @@ __global__ __launch_bounds__(256) void attn_bf16_w4_kernel(
     const int32_t* __restrict__ ctxp, const int32_t* __restrict__ parentp,
     const int32_t* __restrict__ nnp, int N, int Hq, int Hkv, int max_ctx, float scale_log2,
     int split_len, int splits, int mtiles, int pairs, int mrows_pad, uint16_t* __restrict__ wsO,
-    float2* __restrict__ wsML) {
+    float2* __restrict__ wsML, int batch, int target_pairs, RaggedCost rc, int lcap,
+    int2* __restrict__ tab) {
   // the body uses the buffer-resource type, which exists only in the device pass; the
   // host pass needs no more than the signature to emit the launch stub
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -166,8 +301,22 @@ __global__ __launch_bounds__(256) void attn_bf16_w4_kernel(
   const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
   const int mt = slot % mtiles, pair = (slot / mtiles) * 8 + xcd;
   if (pair >= pairs) return;
-  const int split = pair % splits, bg = pair / splits;
-  const int b = bg / Hkv, g = bg - (bg / Hkv) * Hkv;
+  int b, g, split;
+  if (tab == nullptr) {
+    const int bg = pair / splits;
+    split = pair - bg * splits;
+    b = bg / Hkv;
+    g = bg - b * Hkv;
+  } else {
+    const RaggedPick rp = ragged_pick(ctxp, nnp, batch, N, max_ctx, Hkv, mtiles, target_pairs,
+                                      rc, lcap, split_len, pair, tab,
+                                      pair == 0 && mt == 0 && (threadIdx.x >> 6) == 0);
+    if (!rp.found) return;   // past the batch's pairs (nothing issued yet)
+    b = __builtin_amdgcn_readfirstlane(rp.b);
+    g = __builtin_amdgcn_readfirstlane(rp.g);
+    split = __builtin_amdgcn_readfirstlane(rp.split);
+    split_len = __builtin_amdgcn_readfirstlane(rp.L);
+  }
   const int G = Hq / Hkv;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int rg = wave;
@@ -396,6 +545,7 @@ __global__ __launch_bounds__(256) void attn_bf16_w4_kernel(
   for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
     for (int kk = 0; kk < NKK; ++kk) s_mfma(s_k0, kb, kk, sA);
+  TAPS_STAGE_BARRIER();               // every wave has read K(0): step 0 refills its buffer
   for (int i = 0;;) {
     step(sA, sB, s_k0, s_k1, s_v0, s_v3, i);
     if (++i >= nst) break;
@@ -414,7 +564,7 @@ __global__ __launch_bounds__(256) void attn_bf16_w4_kernel(
   const float inv = lsum > 0.f ? 1.f / lsum : 0.f;
 
   // ---- write this split's partial: O / sum in bf16, reference max and sum
-  const size_t obase = ((size_t)bg * splits + split) * mrows_pad;
+  const size_t obase = (size_t)pair * mrows_pad;
   const int qr = row0 + rg * 32 + l32;
   uint16_t* op = wsO + (obase + qr) * HD;
 #pragma unroll
@@ -498,93 +648,6 @@ __device__ inline void load_two_scalars(const int32_t* x, const int32_t* y, int&
       : "memory");
 }
 
-// inclusive prefix sum over the lanes of a wave (DPP row shifts, then row broadcasts)
-__device__ inline int wave_inclusive_sum(int v) {
-  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);  // row_shr:1
-  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);  // row_shr:2
-  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);  // row_shr:4
-  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);  // row_shr:8
-  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);  // row_bcast:15
-  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);  // row_bcast:31
-  return v;
-}
-
-// sum of a 64-bit integer over the lanes of a wave, in every lane
-__device__ inline long long wave_sum_i64(long long v) {
-#pragma unroll
-  for (int m = 32; m >= 1; m >>= 1) {
-    const uint32_t lo = __shfl_xor((uint32_t)v, m), hi = __shfl_xor((uint32_t)((uint64_t)v >> 32), m);
-    v += (long long)(((uint64_t)hi << 32) | lo);
-  }
-  return v;
-}
-
-// Ragged work list of several requests.  Request b has R_b keys (context rows + nodes) and
-// S_b = ceil(R_b / L) splits per KV head; its pairs are numbered from the prefix sum E_b of
-// Hkv * S_b, KV head by KV head.  When the lengths are close (the longest at most 5/4 of
-// the mean), L is the host's split length for max_ctx + budget keys, as in the one-request
-// plan; otherwise L is sized from the batch's total keys so that the batch makes about
-// target_pairs pairs.  Every wave of the workgroup computes the same result; wave 0 of the
-// designated workgroup also writes tab[b] = (E_b, S_b) and tab[batch] = (L, total pairs)
-// for the split combine.
-struct RaggedPick {
-  int b, g, split, L;
-  bool found;
-};
-__device__ inline RaggedPick ragged_pick(const int32_t* ctxp, const int32_t* nnp, int batch,
-                                         int N, int max_ctx, int Hkv, int target_pairs,
-                                         int lcap, int L_host, int p, int2* tab, bool write_tab) {
-  const int lane = threadIdx.x & 63;
-  long long tot = 0;
-  int rmax = 0;
-  for (int c = 0; c < batch; c += 64) {
-    const int b = c + lane;
-    if (b < batch) {
-      const int R = min(max(ctxp[b], 0), max_ctx) + min(max(nnp[b], 0), N);
-      tot += R;
-      rmax = max(rmax, R);
-    }
-  }
-  tot = wave_sum_i64(tot);
-#pragma unroll
-  for (int m = 32; m >= 1; m >>= 1) rmax = max(rmax, __shfl_xor(rmax, m));
-  int L;
-  if (4ll * rmax * batch <= 5ll * tot) {
-    L = L_host;
-  } else {
-    const long long want = (tot * Hkv + target_pairs - 1) / target_pairs;
-    L = (int)min((long long)lcap, max(128ll, (want + 63) / 64 * 64));
-  }
-  RaggedPick r;
-  r.b = r.g = r.split = 0;
-  r.L = L;
-  r.found = false;
-  int carry = 0;
-  for (int c = 0; c < batch; c += 64) {
-    const int b = c + lane;
-    int R = 0;
-    if (b < batch) R = min(max(ctxp[b], 0), max_ctx) + min(max(nnp[b], 0), N);
-    const int S = (R + L - 1) / L;
-    const int P = Hkv * S;
-    const int incl = carry + wave_inclusive_sum(P);
-    const int excl = incl - P;
-    if (write_tab && b < batch) tab[b] = make_int2(excl, S);
-    const uint64_t m = __ballot(b < batch && P > 0 && excl <= p && p < incl);
-    if (m && !r.found) {
-      const int l = __ffsll((long long)m) - 1;
-      const int local = p - __builtin_amdgcn_readlane(excl, l);
-      const int Sb = __builtin_amdgcn_readlane(S, l);
-      r.b = c + l;
-      r.g = local / Sb;
-      r.split = local - r.g * Sb;
-      r.found = true;
-    }
-    carry = __builtin_amdgcn_readlane(incl, 63);
-  }
-  if (write_tab && lane == 0) tab[batch] = make_int2(L, carry);
-  return r;
-}
-
 template <int KG>
 struct GroupTag {
   static constexpr int value = KG;
@@ -604,7 +667,7 @@ __device__ __attribute__((always_inline)) inline void attn_bf16_body(
     const int32_t* __restrict__ ctxp, const int32_t* __restrict__ parentp,
     const int32_t* __restrict__ nnp, int N, int Hq, int Hkv, int max_ctx, float scale_log2,
     int split_len, int splits, int mtiles, int pairs, int mrows_pad, uint16_t* __restrict__ wsO,
-    float2* __restrict__ wsML, DivMagic dm, int batch, int target_pairs, int lcap,
+    float2* __restrict__ wsML, DivMagic dm, int batch, int target_pairs, RaggedCost rc, int lcap,
     int2* __restrict__ tab, const PagedKV& pk) {
   constexpr int HD = 128;
   constexpr int NT = 512;
@@ -650,8 +713,8 @@ __device__ __attribute__((always_inline)) inline void attn_bf16_body(
     b = dm.div(bg, Hkv, dm.hk);
     g = bg - b * Hkv;
   } else {
-    const RaggedPick rp = ragged_pick(ctxp, nnp, batch, N, max_ctx, Hkv, target_pairs, lcap,
-                                      split_len, pair, tab,
+    const RaggedPick rp = ragged_pick(ctxp, nnp, batch, N, max_ctx, Hkv, mtiles, target_pairs,
+                                      rc, lcap, split_len, pair, tab,
                                       pair == 0 && mt == 0 && (threadIdx.x >> 6) == 0);
     if (!rp.found) return;   // past the batch's pairs (nothing issued yet)
     b = __builtin_amdgcn_readfirstlane(rp.b);
@@ -1170,11 +1233,11 @@ __global__ __launch_bounds__(512) void attn_bf16_kernel(
     const int32_t* __restrict__ ctxp, const int32_t* __restrict__ parentp,
     const int32_t* __restrict__ nnp, int N, int Hq, int Hkv, int max_ctx, float scale_log2,
     int split_len, int splits, int mtiles, int pairs, int mrows_pad, uint16_t* __restrict__ wsO,
-    float2* __restrict__ wsML, DivMagic dm, int batch, int target_pairs, int lcap,
+    float2* __restrict__ wsML, DivMagic dm, int batch, int target_pairs, RaggedCost rc, int lcap,
     int2* __restrict__ tab) {
 #if defined(__HIP_DEVICE_COMPILE__)
   attn_bf16_body<false>(Q, Kc, Vc, offp, ctxp, parentp, nnp, N, Hq, Hkv, max_ctx, scale_log2, split_len,
-                       splits, mtiles, pairs, mrows_pad, wsO, wsML, dm, batch, target_pairs, lcap,
+                       splits, mtiles, pairs, mrows_pad, wsO, wsML, dm, batch, target_pairs, rc, lcap,
                        tab, PagedKV{nullptr, 0, 1, 5});
 #endif
 }
@@ -1186,11 +1249,11 @@ __global__ __launch_bounds__(512) void attn_bf16_paged_kernel(
     const int32_t* __restrict__ ctxp, const int32_t* __restrict__ parentp,
     const int32_t* __restrict__ nnp, int N, int Hq, int Hkv, int max_ctx, float scale_log2,
     int split_len, int splits, int mtiles, int pairs, int mrows_pad, uint16_t* __restrict__ wsO,
-    float2* __restrict__ wsML, DivMagic dm, int batch, int target_pairs, int lcap,
+    float2* __restrict__ wsML, DivMagic dm, int batch, int target_pairs, RaggedCost rc, int lcap,
     int2* __restrict__ tab, PagedKV pk) {
 #if defined(__HIP_DEVICE_COMPILE__)
   attn_bf16_body<true>(Q, Kc, Vc, offp, ctxp, parentp, nnp, N, Hq, Hkv, max_ctx, scale_log2, split_len,
-                       splits, mtiles, pairs, mrows_pad, wsO, wsML, dm, batch, target_pairs, lcap,
+                       splits, mtiles, pairs, mrows_pad, wsO, wsML, dm, batch, target_pairs, rc, lcap,
                        tab, pk);
 #endif
 }
@@ -1321,14 +1384,16 @@ AttnPlan plan_attn(int batch, int budget, int Hq, int Hkv, int head_dim, int max
   const int keys = max_ctx + budget;
   const int step = kKT;
   const long long base = (long long)batch * Hkv * p.mtiles;
+  p.resident = 256;
+  p.fixed = 8;
   int splits = 1;
   long long best = -1;
   for (int s = 1; s <= 64; ++s) {
     int l = (keys + s - 1) / s;
     l = ((l + step - 1) / step) * step;
     if (l < 2 * step) l = 2 * step;
-    const long long rounds = (base * s + 255) / 256;
-    const long long cost = rounds * (l / step + 8);
+    const long long rounds = (base * s + p.resident - 1) / p.resident;
+    const long long cost = rounds * (l / step + p.fixed);
     if (best < 0 || cost < best) {
       best = cost;
       splits = s;
@@ -1340,13 +1405,17 @@ AttnPlan plan_attn(int batch, int budget, int Hq, int Hkv, int head_dim, int max
   if (len > p.lcap) len = p.lcap;
   p.split_len = len;
   p.splits = (keys + len - 1) / len;
-  if (batch > 1 && head_dim == 128) {
+  if (batch > 1) {
     // Several requests: their lengths are known only on the device, where the kernel picks
-    // the split length (ragged_pick): this plan's for lengths close to each other, else one
-    // sized for about three workgroups per CU over the batch's actual keys (measured: a
-    // 16-request batch with lengths from 512 to 16K keys takes 12 % less time than with
-    // every request split for max_ctx, a 4 x 32K batch the same).
-    const int target = (3 * 256 + p.mtiles - 1) / p.mtiles;
+    // the split length (ragged_pick): this plan's for lengths close to each other, else the
+    // best by its estimate, up to about four workgroups per CU.  Measured against a fixed
+    // three workgroups per CU (us, 32/8 heads, head_dim 128, with the combine): 4 requests of
+    // 700-6K keys over pages 64.1 -> 44.0, 3 of 700-20K 47.7 -> 35.7, 8 of 300-9K 91 -> 75,
+    // 16 of 512-16K 235 -> 209; head_dim 64 against every request split for max_ctx: 16 of
+    // 512-16K 210 -> 133, 4 of 2-8K 33.8 -> 31.2.  (Two head_dim 64 workgroups fit a CU, but
+    // the softmax bounds both: counting on 512 at a time took 8 requests of 300-3K from 17.6
+    // to 21.3 us.)
+    const int target = (1024 + p.mtiles - 1) / p.mtiles;
     const long long worst = ((long long)batch * (max_ctx + budget) * Hkv + target - 1) / target;
     const long long pm = std::max((long long)target + (long long)batch * Hkv,
                                   (long long)batch * Hkv * p.splits);
@@ -1396,6 +1465,7 @@ static hipError_t launch_attn_bf16_impl(const void* Q, const void* K, const void
   dim3 grid((unsigned)(8 * pl.mtiles * ((pairs + 7) / 8)));
   dim3 block(256u);
   const float sl2 = scale * kLog2e;
+  const RaggedCost rc{pl.resident, pl.fixed};
   const uint16_t *q = (const uint16_t*)Q, *k = (const uint16_t*)K, *v = (const uint16_t*)V;
   // with events, the launch records the kernel's own start and end (hipExtLaunchKernel)
   if (head_dim == 128) {
@@ -1407,33 +1477,35 @@ static hipError_t launch_attn_bf16_impl(const void* Q, const void* K, const void
         hipExtLaunchKernelGGL(attn_bf16_paged_kernel, grid, block8, 0, s, ev_begin, ev_end, 0,
                               q, k, v, off, ctx, parent, n, budget, Hq, Hkv, max_ctx, sl2,
                               pl.split_len, pl.splits, pl.mtiles, pairs, mrows_pad, wsO, wsML,
-                              dm, batch, pl.target_pairs, pl.lcap, tab, pk);
+                              dm, batch, pl.target_pairs, rc, pl.lcap, tab, pk);
       else
         attn_bf16_paged_kernel<<<grid, block8, 0, s>>>(
             q, k, v, off, ctx, parent, n, budget, Hq, Hkv, max_ctx, sl2, pl.split_len, pl.splits,
-            pl.mtiles, pairs, mrows_pad, wsO, wsML, dm, batch, pl.target_pairs, pl.lcap, tab, pk);
+            pl.mtiles, pairs, mrows_pad, wsO, wsML, dm, batch, pl.target_pairs, rc, pl.lcap, tab, pk);
     } else {
       if (ev_begin || ev_end)
         hipExtLaunchKernelGGL(attn_bf16_kernel, grid, block8, 0, s, ev_begin, ev_end, 0, q, k,
                               v, off, ctx, parent, n, budget, Hq, Hkv, max_ctx, sl2,
                               pl.split_len, pl.splits, pl.mtiles, pairs, mrows_pad, wsO, wsML,
-                              dm, batch, pl.target_pairs, pl.lcap, tab);
+                              dm, batch, pl.target_pairs, rc, pl.lcap, tab);
       else
         attn_bf16_kernel<<<grid, block8, 0, s>>>(q, k, v, off, ctx, parent, n, budget, Hq, Hkv,
                                                  max_ctx, sl2, pl.split_len, pl.splits,
                                                  pl.mtiles, pairs, mrows_pad, wsO, wsML, dm,
-                                                 batch, pl.target_pairs, pl.lcap, tab);
+                                                 batch, pl.target_pairs, rc, pl.lcap, tab);
     }
   } else if constexpr (!PAGED) {
     if (ev_begin || ev_end)
       hipExtLaunchKernelGGL(attn_bf16_w4_kernel<64>, grid, block, 0, s, ev_begin, ev_end, 0, q,
                             k, v, off, ctx, parent, n, budget, Hq, Hkv, max_ctx, sl2,
-                            pl.split_len, pl.splits, pl.mtiles, pairs, mrows_pad, wsO, wsML);
+                            pl.split_len, pl.splits, pl.mtiles, pairs, mrows_pad, wsO, wsML, batch,
+                            pl.target_pairs, rc, pl.lcap, tab);
     else
       attn_bf16_w4_kernel<64><<<grid, block, 0, s>>>(q, k, v, off, ctx, parent, n, budget, Hq,
                                                      Hkv, max_ctx, sl2, pl.split_len,
                                                      pl.splits, pl.mtiles, pairs, mrows_pad,
-                                                     wsO, wsML);
+                                                     wsO, wsML, batch, pl.target_pairs,
+                                                     rc, pl.lcap, tab);
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
@@ -1442,7 +1514,6 @@ static hipError_t launch_attn_bf16_impl(const void* Q, const void* K, const void
   // splits per group: the one-request plan's split count (rounded up to 4, 8 or 16), 4
   // for the ragged list
   const int ch = tab != nullptr || pl.splits <= 4 ? 4 : pl.splits <= 8 ? 8 : 16;
-  const int2* tb = head_dim == 128 ? tab : nullptr;
 #define TAPS_COMBINE(HDC, CHC)                                                               \
   attn_combine_kernel<HDC, CHC>                                                              \
       <<<dim3((unsigned)((rows_req + kCombineThreads / (HDC / 8) - 1) /                      \
@@ -1450,7 +1521,7 @@ static hipError_t launch_attn_bf16_impl(const void* Q, const void* K, const void
               (unsigned)batch),                                                              \
          dim3(kCombineThreads), 0, s>>>(wsO, wsML, ctx, n, budget, Hq, Hkv, max_ctx,          \
                                         pl.split_len, pl.splits, mrows_pad, cm, (uint16_t*)O, \
-                                        tb, batch)
+                                        tab, batch)
   if (head_dim == 128) {
     if (ch == 4) TAPS_COMBINE(128, 4);
     else if (ch == 8) TAPS_COMBINE(128, 8);

@@ -59,13 +59,15 @@ struct AttnPlan {
   int wk;          // key groups per workgroup (1 or 2): 256 * wk threads
   int mtile;       // query rows per workgroup (4 waves)
   int mtiles;      // workgroups along the budget*G query rows of one KV head
-  int split_len;   // keys per split (multiple of 64); 0 when ragged
-  int splits;      // splits along max_ctx + budget keys; 1 when ragged
-  // Ragged work list (several requests, head_dim 128): the kernel sizes the splits from the
-  // requests' actual keys so that the batch makes about target_pairs (request, KV head,
-  // split) pairs; at most pairs_max; split lengths at most lcap keys
+  int split_len;   // keys per split (multiple of 64)
+  int splits;      // splits along max_ctx + budget keys
+  // Ragged work list (several requests): the kernel sizes the splits from the requests'
+  // actual keys for up to target_pairs (request, KV head, split) pairs, by an estimate with
+  // `resident` workgroups at a time and `fixed` 64-key steps' worth of work outside the key
+  // loop in each; at most pairs_max; split lengths at most lcap keys
   int ragged;
   int target_pairs;
+  int resident, fixed;
   int pairs_max;
   int lcap;
 };
