@@ -140,6 +140,11 @@ typedef struct {
  * on logits also one 64-bit normaliser partial per chunk, with the learned scorer two). */
 size_t taps_select_workspace_bytes(const taps_select_params *p);
 
+/* Bytes that taps_select can use beyond those with the learned scorer (0 with the others):
+ * each position's top K and K x K edge probabilities.  A workspace of both sizes spreads a
+ * request's positions over the GPU; with less, one workgroup scores them all.  Same results. */
+size_t taps_select_tables_bytes(const taps_select_params *p);
+
 /* Host-only check of the parameters, no device access (the first step of taps_select). */
 taps_status taps_select_validate(const taps_select_params *p);
 

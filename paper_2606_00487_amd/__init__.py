@@ -116,7 +116,8 @@ class Selector:
                                    ctypes.pointer(self._mlp_struct) if mlp is not None else None)
         _lib.check(self.lib, "taps_select_validate", self.lib.taps_select_validate(ctypes.byref(self.p)))
         self.ws_bytes = self.lib.taps_select_workspace_bytes(ctypes.byref(self.p))
-        self.ws = torch.empty(max(self.ws_bytes, 8), dtype=torch.uint8, device=device)
+        nbytes = self.ws_bytes + self.lib.taps_select_tables_bytes(ctypes.byref(self.p))
+        self.ws = torch.empty(max(nbytes, 8), dtype=torch.uint8, device=device)
         self.tree = TreeBuffers.empty(batch, block, K, budget, device)
         self._tree_struct = self.tree.struct()
 
@@ -127,7 +128,7 @@ class Selector:
         st = t.struct() if tree is not None else self._tree_struct
         _lib.check(self.lib, "taps_select",
                    self.lib.taps_select(_ptr(marginals), ctypes.byref(p), ctypes.byref(st),
-                                        _ptr(self.ws), self.ws_bytes, _stream()))
+                                        _ptr(self.ws), self.ws.numel(), _stream()))
         return t
 
     def noalloc(self, marginals: torch.Tensor, tree: TreeBuffers | None = None) -> TreeBuffers:

@@ -28,7 +28,7 @@ MAX_K = 16
 MAX_BUDGET = 512
 
 EXPORTED = [
-    "taps_select_workspace_bytes", "taps_select_validate", "taps_select",
+    "taps_select_workspace_bytes", "taps_select_tables_bytes", "taps_select_validate", "taps_select",
     "tree_verify_attn_workspace_bytes", "tree_verify_attn_validate", "tree_verify_attn",
     "tree_verify_attn_timed", "accept_walk", "kv_commit", "taps_status_string",
     "taps_spec_exp_host", "verify_layer_workspace_bytes", "verify_layer", "taps_select_noalloc",
@@ -91,6 +91,8 @@ def load(path: str = LIB_PATH):
                                   ctypes.c_float, ctypes.c_double, ctypes.c_size_t)
     lib.taps_select_workspace_bytes.argtypes = [P(SelectParams)]
     lib.taps_select_workspace_bytes.restype = sz
+    lib.taps_select_tables_bytes.argtypes = [P(SelectParams)]
+    lib.taps_select_tables_bytes.restype = sz
     lib.taps_select_validate.argtypes = [P(SelectParams)]
     lib.taps_select_validate.restype = i32
     lib.taps_select.argtypes = [vp, P(SelectParams), P(Tree), vp, sz, vp]

@@ -133,6 +133,11 @@ size_t taps_select_workspace_bytes(const taps_select_params* p) {
   return cand + (needs_z(p) ? part : 0) + (p->scorer == TAPS_SCORER_LEARNED ? part : 0);
 }
 
+size_t taps_select_tables_bytes(const taps_select_params* p) {
+  if (select_check(p) != TAPS_OK || p->scorer != TAPS_SCORER_LEARNED) return 0;
+  return (size_t)p->batch * p->block * p->K * (1 + p->K) * sizeof(uint64_t);
+}
+
 taps_status taps_select(const void* marginals, const taps_select_params* p, const taps_tree* out,
                         void* ws, size_t ws_bytes, hipStream_t stream) {
   const taps_status st = select_check(p);
@@ -150,6 +155,9 @@ taps_status taps_select(const void* marginals, const taps_select_params* p, cons
                          stream) != hipSuccess)
     return TAPS_ERR_HIP;
   int64_t *zpart = nullptr, *spart = nullptr;
+  // the learned scorer's tables, where the workspace has room for them after its lists
+  const size_t tb = taps_select_tables_bytes(p);
+  void* tables = tb && ws_bytes - need >= tb ? (char*)ws + need : nullptr;
   if (needs_z(p)) {
     zpart = (int64_t*)((char*)ws + (size_t)rows * plan.chunks * p->K * sizeof(uint64_t));
     if (p->scorer == TAPS_SCORER_LEARNED) spart = zpart + (size_t)rows * plan.chunks * kZSub;
@@ -157,7 +165,7 @@ taps_status taps_select(const void* marginals, const taps_select_params* p, cons
                           zpart, spart, stream) != hipSuccess)
       return TAPS_ERR_HIP;
   }
-  if (launch_select(marginals, *p, plan, (const uint64_t*)ws, zpart, spart, *out, stream) !=
+  if (launch_select(*p, plan, (const uint64_t*)ws, zpart, spart, tables, *out, stream) !=
       hipSuccess)
     return TAPS_ERR_HIP;
   return TAPS_OK;

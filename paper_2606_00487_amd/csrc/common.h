@@ -37,8 +37,9 @@ TopkPlan plan_topk(int vocab, int rows, int dtype);
 hipError_t launch_topk_chunks(const void* marg, int dtype, int rows, int vocab, int K,
                               const TopkPlan& plan, uint64_t* cand, hipStream_t s);
 
-hipError_t launch_select(const void* marg, const taps_select_params& p, const TopkPlan& plan,
-                         const uint64_t* cand, const int64_t* zpart, const int64_t* spart,
+// tables (learned scorer): taps_select_tables_bytes for the rows' top K and q_cond, or null
+hipError_t launch_select(const taps_select_params& p, const TopkPlan& plan, const uint64_t* cand,
+                         const int64_t* zpart, const int64_t* spart, void* tables,
                          const taps_tree& out, hipStream_t s);
 
 // Integer partials of a row's full-vocabulary sums per top-K chunk (one workgroup each)

@@ -501,195 +501,379 @@ __device__ __attribute__((always_inline)) inline int select_sequential(Shared& s
   return n;
 }
 
-// LEARNED: the learned scorer's instance (its q_cond table and Phase B2); the other
-// scorers run an instance without that code, so their kernel stays smaller.
-template <int SLOTS, bool LEARNED>
+// The candidate lists of the marginal rows and what a row's merge needs of the call
+struct RowLists {
+  const uint64_t* cand;
+  const int64_t *zpart, *spart;
+  int chunks, K, kind, marginal;
+  double beta;
+  int32_t* tidx;
+  float* tval;
+};
+
+// Phase A of one row, by one wave: the row's top K into top[] (and, if write, the outputs),
+// its Eq. 1 terms into e_[] and edge probabilities into c_[], or for the learned scorer
+// (LEARNED) LOG(Z) and the entropy into *lz and *ent (q_cond comes later).  rowc and heads
+// are the wave's LDS scratch (kRowCap and kWave entries); JM 64-entry slices hold the lists.
+template <int JM, bool LEARNED>
+__device__ __attribute__((always_inline)) inline void merge_row(
+    const RowLists& a, size_t row, bool write, uint64_t* rowc, uint64_t* heads, uint64_t* top,
+    double* e_, double* c_, double* lz, double* ent) {
+  const int lane = threadIdx.x & (kWave - 1);
+  const int K = a.K, chunks = a.chunks, CK = chunks * K;
+  const uint64_t* rc = a.cand + row * CK;
+  uint64_t v[JM];
+#pragma unroll
+  for (int j = 0; j < JM; ++j) {
+    const int e = j * kWave + lane;
+    const uint64_t x = rc[min(e, CK - 1)];
+    v[j] = e < CK ? x : 0ull;
+  }
+  const uint64_t hx = rc[(size_t)min(lane, chunks - 1) * K];
+  const uint64_t head = lane < chunks ? hx : 0ull;
+  // heads that beat this lane's head, read back from LDS eight at a time (every lane
+  // reads the same address; the heads of lanes >= chunks are 0 and beat nothing)
+  heads[lane] = head;
+  wave_fence();
+  int beat = 0;
+  for (int t0 = 0; t0 < chunks; t0 += 8) {
+    uint64_t hv[8];
+#pragma unroll
+    for (int t = 0; t < 8; ++t) hv[t] = heads[t0 + t];
+#pragma unroll
+    for (int t = 0; t < 8; ++t) beat += hv[t] > head ? 1 : 0;
+  }
+  const int nheads = __popcll(__ballot(head != 0ull));
+  uint64_t T = 1ull;  // fewer non-empty chunks than K: every entry is a candidate
+  if (nheads >= K) {
+    const int tl = __ffsll((long long)__ballot(head != 0ull && beat == K - 1)) - 1;
+    T = read_lane_u64(head, tl);
+  }
+  // compact the entries >= T (at most K*K of them) in order
+  int total = 0;
+#pragma unroll
+  for (int j = 0; j < JM; ++j) {
+    const uint64_t m = __ballot(v[j] >= T);
+    const int pos = total + lanes_below(m);
+    if (v[j] >= T && pos < kRowCap) rowc[pos] = v[j];
+    total += __popcll(m);
+  }
+  total = total < kRowCap ? total : kRowCap;
+  wave_fence();
+  const size_t orow = row * K;
+  // More than a wave's worth of candidates (flat rows): the K-th largest of them, T2,
+  // by a descent over the key bits in which the candidates differ (the others are
+  // common to all of them, so T2 has them too); the K entries >= T2 (keys are unique)
+  // replace the candidate list.
+  if (total > kWave) {   // uniform
+    constexpr int JC = kRowCap / kWave;
+    uint64_t cv[JC];
+    uint64_t lor = 0ull, land = ~0ull;   // over this lane's candidates
+#pragma unroll
+    for (int j = 0; j < JC; ++j) {
+      const int e = j * kWave + lane;
+      const uint64_t x = rowc[e];
+      cv[j] = e < total ? x : 0ull;
+      lor |= e < total ? x : 0ull;
+      land &= e < total ? x : ~0ull;
+    }
+    const uint64_t gor = ((uint64_t)wave_or_u32((uint32_t)(lor >> 32)) << 32) |
+                         wave_or_u32((uint32_t)lor);
+    const uint64_t gand = ((uint64_t)wave_and_u32((uint32_t)(land >> 32)) << 32) |
+                          wave_and_u32((uint32_t)land);
+    const uint64_t diff = gor ^ gand;
+    uint64_t T2 = gand & ~diff;
+    for (uint64_t m = diff; m != 0ull;) {   // uniform
+      const int bit = 63 - __clzll((long long)m);
+      m &= ~(1ull << bit);
+      const uint64_t c = T2 | (1ull << bit);
+      int nc = 0;
+#pragma unroll
+      for (int j = 0; j < JC; ++j)
+        if (j * kWave < total) nc += __popcll(__ballot(cv[j] >= c));
+      if (nc >= K) T2 = c;
+    }
+    wave_fence();   // every lane has read the list before it is overwritten
+    int kept = 0;
+#pragma unroll
+    for (int j = 0; j < JC; ++j) {
+      const uint64_t m = __ballot(cv[j] >= T2);
+      const int pos = kept + lanes_below(m);
+      if (cv[j] >= T2) rowc[pos] = cv[j];
+      kept += __popcll(m);
+    }
+    total = kept;   // == K
+    wave_fence();
+  }
+  // exact ranks of the (at most 64) candidates, one per lane, read back from LDS
+  // eight at a time; the entry of rank r < K is the row's r-th candidate
+  {
+    const uint64_t mx = rowc[lane];
+    const uint64_t mine = lane < total ? mx : 0ull;
+    int rank = 0;
+    for (int t0 = 0; t0 < total; t0 += 8) {
+      uint64_t rv[8];
+#pragma unroll
+      for (int t = 0; t < 8; ++t) {
+        const uint64_t x = rowc[t0 + t];
+        rv[t] = t0 + t < total ? x : 0ull;
+      }
+#pragma unroll
+      for (int t = 0; t < 8; ++t) rank += rv[t] > mine ? 1 : 0;
+    }
+    if (lane < total && rank < K) {
+      top[rank] = mine;
+      if (write) {
+        a.tidx[orow + rank] = (int32_t)cand_index(mine);
+        if (a.tval) a.tval[orow + rank] = value_from_key((uint32_t)(mine >> 32));
+      }
+    }
+  }
+  for (int r = total + lane; r < K; r += kWave) {   // a row with fewer than K entries
+    top[r] = 0ull;
+    if (write) {
+      a.tidx[orow + r] = -1;
+      if (a.tval) a.tval[orow + r] = value_from_key(0u);
+    }
+  }
+  wave_fence();
+  // Eq. 1 for this row (lane r < K): e_r, then c_r = e_r / Z with Z summed in rank order
+  if (lane < K) {
+    const uint64_t k = top[lane];
+    const double x = k ? (double)value_from_key((uint32_t)(k >> 32)) : (double)__uint_as_float(0x7FC00000u);
+    double e;
+    if (a.kind == TAPS_LOGITS) {
+      const uint64_t k0 = top[0];
+      const double x0 = k0 ? (double)value_from_key((uint32_t)(k0 >> 32)) : x;
+      e = spec_exp(a.beta * (x - x0));
+    } else {
+      e = x > 0.0 ? x : 0.0;
+    }
+    e_[lane] = e;
+  }
+  wave_fence();
+  if constexpr (LEARNED) {
+    // learned scorer: LOG(Z) and the entropy LOG(Z) - S / Z of the row from the exact
+    // sums of its integer partials (multiples of 2^-42); q_cond comes later
+    const int zn = chunks * kZSub;
+    const int64_t* zr = a.zpart + row * zn;
+    const int64_t* sr = a.spart + row * zn;
+    int64_t zp = 0, sp = 0;
+    for (int c0 = lane; c0 < zn; c0 += kWave) {
+      zp += zr[c0];
+      sp += sr[c0];
+    }
+    const int64_t zi = wave_sum_i64(zp), si = wave_sum_i64(sp);
+    if (lane == 0) {
+      const double Z = (double)zi * 0x1p-42, S = (double)si * 0x1p-42;
+      const double logz = zi > 0 ? spec_log(Z) : __longlong_as_double(0x7FF8000000000000ll);
+      *lz = logz;
+      *ent = logz - S / Z;
+    }
+  } else if (a.zpart) {
+    // marginal scorer, logits (beta is 1): the full-vocabulary normaliser is the exact
+    // sum of the row's integer partials (multiples of 2^-42)
+    const int zn = chunks * kZSub;
+    const int64_t* zr = a.zpart + row * zn;
+    int64_t zp = 0;
+    for (int c0 = lane; c0 < zn; c0 += kWave) zp += zr[c0];
+    const int64_t zi = wave_sum_i64(zp);
+    const double Z = (double)zi * 0x1p-42;
+    if (lane < K) c_[lane] = Z > 0.0 ? e_[lane] / Z : 0.0;
+  } else if (a.kind == TAPS_PROBS && a.marginal) {
+    // the probability itself (e = x if x > 0, else 0), clamped to 1
+    if (lane < K) c_[lane] = fmin(e_[lane], 1.0);
+  } else if (lane < K) {
+    double Z = 0.0;
+    for (int j = 0; j < K; ++j) Z = Z + e_[j];
+    const bool ok = Z > 0.0 && Z <= 1.7976931348623157e308;
+    c_[lane] = ok ? e_[lane] / Z : 0.0;
+  }
+}
+
+// Learned scorer: one row i of one request per workgroup (grid: batch * D).  Merges the row
+// (wave 0) and the one above it, whose top K are the parents (wave 1), while the other waves
+// stage the weights; then the row's K x K q_cond values.  One workgroup for all rows of a
+// request took 27.7 us with the selection (16 rows, K 8, emb 16, hidden 32): fp64 sums on
+// one CU.  Rows on CUs of their own leave the chain of memory round trips as the bound.
+// The selection call: 41.0 -> 28.8 us, 8 requests of 12 rows 46.1 -> 37.9.
+// In LDS: the weights (W1, b1, w2 as fp32), the embeddings of the parents (row 0: the
+// root's token) and children (zeros for no token) at an odd row stride, each unit's three
+// edge-feature weights and its w2 widened to fp64, and per hidden unit k of a chunk of KC
+// the parent part b1[k] + P_k of each parent, then the child part C_k of each child, at an
+// odd stride.  Each edge then adds its five terms per unit.
+constexpr int kRowThreads = 512;
+struct LearnedRowLayout {
+  int wsz, ES, esz, PS, KC;   // floats, row stride, floats; doubles per unit, units per chunk
+  size_t bytes;
+};
+__host__ __device__ inline LearnedRowLayout learned_row_layout(int D, int K, int d, int h) {
+  LearnedRowLayout l;
+  const int S = D > 1 ? 2 * K : K + 1;   // parents and children of a row, at most
+  l.wsz = (h * (2 * d + 3) + 2 * h + 1) & ~1;
+  l.ES = d | 1;
+  l.esz = (S * l.ES + 1) & ~1;
+  l.PS = S | 1;
+  // learned_layout accepts a call only if all rows' embeddings and at least one unit's parts
+  // fit sizeof(Scratch); a single row's need no more (and 8 bytes for the odd stride)
+  const long long fixed = 4ll * (l.wsz + l.esz) + 32ll * h;
+  const long long kc = ((long long)sizeof(Scratch) + 64 - fixed) / (8ll * l.PS);
+  l.KC = (int)(kc < h ? kc : h);
+  l.bytes = (size_t)(fixed + 8ll * l.PS * l.KC);
+  return l;
+}
+__global__ __launch_bounds__(kRowThreads) void learned_rows_kernel(
+    int D, RowLists lists, ScorerArgs mlp, uint64_t* __restrict__ rtop,
+    double* __restrict__ qtab) {
+  __shared__ uint64_t s_rowc[2][kRowCap], s_heads[2][kWave + 2];
+  __shared__ uint64_t s_top[2][TAPS_MAX_K];   // [0] the children, [1] the parents (row > 0)
+  __shared__ double s_e[2][TAPS_MAX_K], s_lz[2], s_ent[2];
+  __shared__ double s_lg[TAPS_MAX_K * TAPS_MAX_K], s_ex[TAPS_MAX_K * TAPS_MAX_K];
+  extern __shared__ double s_dyn[];
+  const int K = lists.K, d = mlp.d, h = mlp.h, F = 2 * d + 3;
+  const int b = blockIdx.x / D, i = blockIdx.x - b * D;
+  const int tid = threadIdx.x, wave = tid / kWave;
+  const LearnedRowLayout lay = learned_row_layout(D, K, d, h);
+  float* Ws = reinterpret_cast<float*>(s_dyn);
+  float* Es = Ws + lay.wsz;
+  double* Wd = reinterpret_cast<double*>(Es + lay.esz);
+  double* part = Wd + 4 * h;
+  const int ES = lay.ES, PS = lay.PS, KC = lay.KC;
+  const int np = i == 0 ? 1 : K, S = np + K, edges = np * K;
+  if (wave < 2) {
+    if (wave == 0 || i > 0) {
+      const size_t row = blockIdx.x - wave;
+      if (lists.chunks * K <= 4 * kWave)
+        merge_row<4, true>(lists, row, wave == 0, s_rowc[wave], s_heads[wave], s_top[wave],
+                           s_e[wave], nullptr, &s_lz[wave], &s_ent[wave]);
+      else
+        merge_row<16, true>(lists, row, wave == 0, s_rowc[wave], s_heads[wave], s_top[wave],
+                            s_e[wave], nullptr, &s_lz[wave], &s_ent[wave]);
+    }
+  } else {
+    const int t0 = tid - 2 * kWave, nt = kRowThreads - 2 * kWave;
+    for (int j = t0; j < h * F; j += nt) Ws[j] = mlp.W1[j];
+    for (int j = t0; j < h; j += nt) {
+      const float w2j = mlp.w2[j];
+      Ws[h * F + j] = mlp.b1[j];
+      Ws[h * F + h + j] = w2j;
+      Wd[4 * j] = (double)mlp.W1[j * F + 2 * d];
+      Wd[4 * j + 1] = (double)mlp.W1[j * F + 2 * d + 1];
+      Wd[4 * j + 2] = (double)mlp.W1[j * F + 2 * d + 2];
+      Wd[4 * j + 3] = (double)w2j;
+    }
+  }
+  __syncthreads();
+  for (int j = tid; j < S * d; j += kRowThreads) {
+    const int es = j / d, jj = j - es * d;
+    int tok = -1;
+    if (i == 0 && es == 0) {
+      tok = mlp.root_token[b];
+      if (tok >= mlp.vocab) tok = -1;   // outside the vocabulary: a zero embedding
+    } else {
+      const uint64_t kc = es < np ? s_top[1][es] : s_top[0][es - np];
+      if (kc) tok = (int)cand_index(kc);
+    }
+    Es[es * ES + jj] = tok >= 0 ? mlp.emb[(size_t)tok * d + jj] : 0.0f;
+  }
+  for (int ed = tid; ed < edges; ed += kRowThreads)
+    s_lg[ed] = s_top[0][ed % K] ? (double)mlp.b2 : -INFINITY;
+  if (tid < K) rtop[(size_t)blockIdx.x * K + tid] = s_top[0][tid];
+  __syncthreads();
+  const double M = (double)value_from_key((uint32_t)(s_top[0][0] >> 32));
+  for (int k0 = 0; k0 < h; k0 += KC) {
+    const int kn = min(KC, h - k0);
+    // the embedding sums, in index order from 0: one slot and unit per thread
+    for (int t = tid; t < kn * S; t += kRowThreads) {
+      const int sl = t / kn, kk = t - sl * kn;
+      const bool child = sl >= np;
+      const float* e = Es + sl * ES;
+      const float* w = Ws + (k0 + kk) * F + (child ? d : 0);
+      double acc = 0.0;
+      for (int j = 0; j < d; ++j) acc = acc + (double)w[j] * (double)e[j];
+      part[kk * PS + sl] = child ? acc : (double)Ws[h * F + k0 + kk] + acc;
+    }
+    __syncthreads();
+    // each edge's logit over the chunk's units, four units at a time
+    for (int ed = tid; ed < edges; ed += kRowThreads) {
+      const int pr = ed / K, r = ed - pr * K;
+      const uint64_t kc = s_top[0][r];
+      if (!kc) continue;
+      const double x = (double)value_from_key((uint32_t)(kc >> 32));
+      const double lp = (x - M) - s_lz[0];
+      const double depth = (double)(i + 1), H = s_ent[0];
+      double logit = s_lg[ed];
+      for (int kk = 0; kk < kn; kk += 4) {
+        double av[4], w2v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const int k = min(kk + u, kn - 1);
+          const double* w = Wd + 4 * (k0 + k);
+          double a = part[k * PS + pr] + part[k * PS + np + r];
+          a = a + w[0] * depth;
+          a = a + w[1] * lp;
+          a = a + w[2] * H;
+          av[u] = a > 0.0 ? a : 0.0;
+          w2v[u] = w[3];
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          if (kk + u < kn) logit = logit + w2v[u] * av[u];
+      }
+      s_lg[ed] = logit;
+    }
+    __syncthreads();
+  }
+  // sibling softmax of each parent's K logits, one child per thread: the terms EXP(l - max),
+  // then the rank-order sum and the quotients.  Row 0 has only the root as parent; its other
+  // parent ranks take the root's entries.
+  for (int t = tid; t < edges; t += kRowThreads) {
+    const double* lg = s_lg + t / K * K;
+    double m = -INFINITY;
+    for (int j = 0; j < K; ++j) m = fmax(m, lg[j]);   // NaN logits ignored
+    s_ex[t] = spec_exp(s_lg[t] - m);
+  }
+  __syncthreads();
+  for (int t = tid; t < K * K; t += kRowThreads) {
+    const int pr = t / K, r = t - pr * K;
+    const double* e = s_ex + (i == 0 ? 0 : pr) * K;
+    double Z = 0.0;
+    for (int j = 0; j < K; ++j) Z = Z + e[j];
+    const bool ok = Z > 0.0 && Z <= 1.7976931348623157e308;
+    qtab[(size_t)blockIdx.x * K * K + t] = ok ? e[r] / Z : 0.0;
+  }
+}
+
+// MODE kOwnRows: the sibling and marginal scorers, which merge the rows here.  kTables: the
+// learned scorer from the rows' top K (rtop) and the q_cond table (qtab) that
+// learned_rows_kernel left.  kInPlace: the learned scorer with a workspace of the least size,
+// which has no room for those: rows and q_cond on this one workgroup.
+enum { kOwnRows, kTables, kInPlace };
+template <int SLOTS, int MODE>
 __global__ __launch_bounds__(kThreadsA) void select_kernel(
     int D, int K, int N, int kind, double lambda1, double lambda2, double tau, double beta,
     int chunks, int marginal, const uint64_t* __restrict__ cand,
     const int64_t* __restrict__ zpart, const int64_t* __restrict__ spart, ScorerArgs mlp,
-    int32_t* __restrict__ o_parent,
+    const uint64_t* __restrict__ rtop, const double* __restrict__ qtab, int32_t* __restrict__ o_parent,
     int32_t* __restrict__ o_token, int32_t* __restrict__ o_depth, int32_t* __restrict__ o_rank,
     double* __restrict__ o_q, int32_t* __restrict__ o_n, int32_t* __restrict__ o_tidx,
     float* __restrict__ o_tval) {
   __shared__ Shared sh;
+  extern __shared__ double s_c3[];   // learned scorer only
   const int b = blockIdx.x;
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
-  const bool learned = LEARNED && spart != nullptr;   // the entropy partials come with it
 
   // ---------------- Phase A: row merge (one wave per row)
   // Loads below take clamped (in-bounds) addresses and are issued unconditionally, the
   // values past the end being masked afterwards, so that each batch costs one round trip.
-  {
+  if constexpr (MODE == kTables) {
+    for (int j = tid; j < D * K; j += kThreadsA)
+      sh.top[j / K][j % K] = rtop[(size_t)b * D * K + j];
+    for (int j = tid; j < D * K * K; j += kThreadsA) s_c3[j] = qtab[(size_t)b * D * K * K + j];
+  } else {
     PhaseA& A = sh.x.a;
+    const RowLists lists{cand, zpart, spart, chunks, K, kind, marginal, beta, o_tidx, o_tval};
     const int CK = chunks * K;
-    auto merge_row = [&](auto jm_tag, int i) __attribute__((always_inline)) {
-      constexpr int JM = decltype(jm_tag)::value;   // 64-entry slices of the row's lists
-      const uint64_t* rc = cand + ((size_t)b * D + i) * CK;
-      uint64_t v[JM];
-#pragma unroll
-      for (int j = 0; j < JM; ++j) {
-        const int e = j * kWave + lane;
-        const uint64_t x = rc[min(e, CK - 1)];
-        v[j] = e < CK ? x : 0ull;
-      }
-      const uint64_t hx = rc[(size_t)min(lane, chunks - 1) * K];
-      const uint64_t head = lane < chunks ? hx : 0ull;
-      // heads that beat this lane's head, read back from LDS eight at a time (every lane
-      // reads the same address; the heads of lanes >= chunks are 0 and beat nothing)
-      A.heads[wave][lane] = head;
-      wave_fence();
-      int beat = 0;
-      for (int t0 = 0; t0 < chunks; t0 += 8) {
-        uint64_t hv[8];
-#pragma unroll
-        for (int t = 0; t < 8; ++t) hv[t] = A.heads[wave][t0 + t];
-#pragma unroll
-        for (int t = 0; t < 8; ++t) beat += hv[t] > head ? 1 : 0;
-      }
-      const int nheads = __popcll(__ballot(head != 0ull));
-      uint64_t T = 1ull;  // fewer non-empty chunks than K: every entry is a candidate
-      if (nheads >= K) {
-        const int tl = __ffsll((long long)__ballot(head != 0ull && beat == K - 1)) - 1;
-        T = read_lane_u64(head, tl);
-      }
-      // compact the entries >= T (at most K*K of them) in order
-      int total = 0;
-#pragma unroll
-      for (int j = 0; j < JM; ++j) {
-        const uint64_t m = __ballot(v[j] >= T);
-        const int pos = total + lanes_below(m);
-        if (v[j] >= T && pos < kRowCap) A.rowc[wave][pos] = v[j];
-        total += __popcll(m);
-      }
-      total = total < kRowCap ? total : kRowCap;
-      wave_fence();
-      const size_t orow = ((size_t)b * D + i) * K;
-      // More than a wave's worth of candidates (flat rows): the K-th largest of them, T2,
-      // by a descent over the key bits in which the candidates differ (the others are
-      // common to all of them, so T2 has them too); the K entries >= T2 (keys are unique)
-      // replace the candidate list.
-      if (total > kWave) {   // uniform
-        constexpr int JC = kRowCap / kWave;
-        uint64_t cv[JC];
-        uint64_t lor = 0ull, land = ~0ull;   // over this lane's candidates
-#pragma unroll
-        for (int j = 0; j < JC; ++j) {
-          const int e = j * kWave + lane;
-          const uint64_t x = A.rowc[wave][e];
-          cv[j] = e < total ? x : 0ull;
-          lor |= e < total ? x : 0ull;
-          land &= e < total ? x : ~0ull;
-        }
-        const uint64_t gor = ((uint64_t)wave_or_u32((uint32_t)(lor >> 32)) << 32) |
-                             wave_or_u32((uint32_t)lor);
-        const uint64_t gand = ((uint64_t)wave_and_u32((uint32_t)(land >> 32)) << 32) |
-                              wave_and_u32((uint32_t)land);
-        const uint64_t diff = gor ^ gand;
-        uint64_t T2 = gand & ~diff;
-        for (uint64_t m = diff; m != 0ull;) {   // uniform
-          const int bit = 63 - __clzll((long long)m);
-          m &= ~(1ull << bit);
-          const uint64_t c = T2 | (1ull << bit);
-          int nc = 0;
-#pragma unroll
-          for (int j = 0; j < JC; ++j)
-            if (j * kWave < total) nc += __popcll(__ballot(cv[j] >= c));
-          if (nc >= K) T2 = c;
-        }
-        wave_fence();   // every lane has read the list before it is overwritten
-        int kept = 0;
-#pragma unroll
-        for (int j = 0; j < JC; ++j) {
-          const uint64_t m = __ballot(cv[j] >= T2);
-          const int pos = kept + lanes_below(m);
-          if (cv[j] >= T2) A.rowc[wave][pos] = cv[j];
-          kept += __popcll(m);
-        }
-        total = kept;   // == K
-        wave_fence();
-      }
-      // exact ranks of the (at most 64) candidates, one per lane, read back from LDS
-      // eight at a time; the entry of rank r < K is the row's r-th candidate
-      {
-        const uint64_t mx = A.rowc[wave][lane];
-        const uint64_t mine = lane < total ? mx : 0ull;
-        int rank = 0;
-        for (int t0 = 0; t0 < total; t0 += 8) {
-          uint64_t rv[8];
-#pragma unroll
-          for (int t = 0; t < 8; ++t) {
-            const uint64_t x = A.rowc[wave][t0 + t];
-            rv[t] = t0 + t < total ? x : 0ull;
-          }
-#pragma unroll
-          for (int t = 0; t < 8; ++t) rank += rv[t] > mine ? 1 : 0;
-        }
-        if (lane < total && rank < K) {
-          sh.top[i][rank] = mine;
-          o_tidx[orow + rank] = (int32_t)cand_index(mine);
-          if (o_tval) o_tval[orow + rank] = value_from_key((uint32_t)(mine >> 32));
-        }
-      }
-      for (int r = total + lane; r < K; r += kWave) {   // a row with fewer than K entries
-        sh.top[i][r] = 0ull;
-        o_tidx[orow + r] = -1;
-        if (o_tval) o_tval[orow + r] = value_from_key(0u);
-      }
-      wave_fence();
-      // Eq. 1 for this row (lane r < K): e_r, then c_r = e_r / Z with Z summed in rank order
-      if (lane < K) {
-        const uint64_t k = sh.top[i][lane];
-        const double x = k ? (double)value_from_key((uint32_t)(k >> 32)) : (double)__uint_as_float(0x7FC00000u);
-        double e;
-        if (kind == TAPS_LOGITS) {
-          const uint64_t k0 = sh.top[i][0];
-          const double x0 = k0 ? (double)value_from_key((uint32_t)(k0 >> 32)) : x;
-          e = spec_exp(beta * (x - x0));
-        } else {
-          e = x > 0.0 ? x : 0.0;
-        }
-        sh.e[i][lane] = e;
-      }
-      wave_fence();
-      if (learned) {
-        // learned scorer: LOG(Z) and the entropy LOG(Z) - S / Z of the row from the exact
-        // sums of its integer partials (multiples of 2^-42); q_cond comes later
-        const int zn = chunks * kZSub;
-        const int64_t* zr = zpart + ((size_t)b * D + i) * zn;
-        const int64_t* sr = spart + ((size_t)b * D + i) * zn;
-        int64_t zp = 0, sp = 0;
-        for (int c0 = lane; c0 < zn; c0 += kWave) {
-          zp += zr[c0];
-          sp += sr[c0];
-        }
-        const int64_t zi = wave_sum_i64(zp), si = wave_sum_i64(sp);
-        if (lane == 0) {
-          const double Z = (double)zi * 0x1p-42, S = (double)si * 0x1p-42;
-          const double lz = zi > 0 ? spec_log(Z) : __longlong_as_double(0x7FF8000000000000ll);
-          sh.lz[i] = lz;
-          sh.ent[i] = lz - S / Z;
-        }
-      } else if (zpart) {
-        // marginal scorer, logits (beta is 1): the full-vocabulary normaliser is the exact
-        // sum of the row's integer partials (multiples of 2^-42)
-        const int zn = chunks * kZSub;
-        const int64_t* zr = zpart + ((size_t)b * D + i) * zn;
-        int64_t zp = 0;
-        for (int c0 = lane; c0 < zn; c0 += kWave) zp += zr[c0];
-        const int64_t zi = wave_sum_i64(zp);
-        const double Z = (double)zi * 0x1p-42;
-        if (lane < K) sh.c[i][lane] = Z > 0.0 ? sh.e[i][lane] / Z : 0.0;
-      } else if (kind == TAPS_PROBS && marginal) {
-        // the probability itself (e = x if x > 0, else 0), clamped to 1
-        if (lane < K) sh.c[i][lane] = fmin(sh.e[i][lane], 1.0);
-      } else if (lane < K) {
-        double Z = 0.0;
-        for (int j = 0; j < K; ++j) Z = Z + sh.e[i][j];
-        const bool ok = Z > 0.0 && Z <= 1.7976931348623157e308;
-        sh.c[i][lane] = ok ? sh.e[i][lane] / Z : 0.0;
-      }
-    };
     // Two rows per wave, one per 32-lane half (row 2 pr + h in half h), for the common
     // shapes: K <= 8 (at most K*K <= 64 entries reach the threshold, two per lane), at
     // most 32 chunks (one head per lane) and 256 list entries.  Same steps and arithmetic
@@ -721,7 +905,7 @@ __global__ __launch_bounds__(kThreadsA) void select_kernel(
           const int c0 = q * 32 + hl;
           const int64_t z = zpart[zo + min(c0, zn - 1)];
           zp += c0 < zn ? z : 0;
-          if (learned) {
+          if constexpr (MODE == kInPlace) {
             const int64_t t = spart[zo + min(c0, zn - 1)];
             sp += c0 < zn ? t : 0;
           }
@@ -814,7 +998,7 @@ __global__ __launch_bounds__(kThreadsA) void select_kernel(
         sh.e[i][hl] = e;
       }
       wave_fence();
-      if (learned) {
+      if constexpr (MODE == kInPlace) {
         // learned scorer: LOG(Z) and the entropy LOG(Z) - S / Z of the row from the exact
         // sums of its integer partials (multiples of 2^-42); q_cond comes later
         const int64_t zi = half_sum_i64(zp), si = half_sum_i64(sp);
@@ -848,8 +1032,13 @@ __global__ __launch_bounds__(kThreadsA) void select_kernel(
       }
     } else {
       for (int i = wave; i < D; i += kWavesA) {
-        if (CK <= 4 * kWave) merge_row(IntC<4>(), i);
-        else merge_row(IntC<16>(), i);
+        const size_t row = (size_t)b * D + i;
+        if (CK <= 4 * kWave)
+          merge_row<4, MODE == kInPlace>(lists, row, true, A.rowc[wave], A.heads[wave], sh.top[i],
+                                         sh.e[i], sh.c[i], &sh.lz[i], &sh.ent[i]);
+        else
+          merge_row<16, MODE == kInPlace>(lists, row, true, A.rowc[wave], A.heads[wave],
+                                          sh.top[i], sh.e[i], sh.c[i], &sh.lz[i], &sh.ent[i]);
       }
     }
   }
@@ -857,9 +1046,8 @@ __global__ __launch_bounds__(kThreadsA) void select_kernel(
   if (tid <= D) sh.den[tid] = lambda1 + lambda2 * (double)tid;
   __syncthreads();
   // ---------------- learned scorer: q_cond table c3[i][parent rank][child rank] (all waves)
-  extern __shared__ double s_c3[];
-  double* c3 = learned ? s_c3 : nullptr;
-  if (learned) {
+  double* c3 = MODE != kOwnRows ? s_c3 : nullptr;
+  if constexpr (MODE == kInPlace) {
     const int F = 2 * mlp.d + 3, d = mlp.d, h = mlp.h;
     const int edges = D * K * K, DK = D * K;
     // The scratch area (free until Phase C) holds, in order: the weights (W1, b1, w2 as
@@ -1303,18 +1491,37 @@ hipError_t launch_marginal_z(const void* marg, int dtype, int rows, int vocab, i
 
 int learned_chunk_units(int D, int K, int d, int h) { return learned_layout(D, K, d, h).KC; }
 
-hipError_t launch_select(const void* /*marg*/, const taps_select_params& p, const TopkPlan& plan,
-                         const uint64_t* cand, const int64_t* zpart, const int64_t* spart,
+hipError_t launch_select(const taps_select_params& p, const TopkPlan& plan, const uint64_t* cand,
+                         const int64_t* zpart, const int64_t* spart, void* tables,
                          const taps_tree& out, hipStream_t s) {
   dim3 grid((unsigned)p.batch), block(kThreadsA);
   const int slots = (p.budget + kWave - 1) / kWave;
   const int marginal = p.scorer == TAPS_SCORER_MARGINAL;
+  uint64_t* rtop = nullptr;
+  double* qtab = nullptr;
   ScorerArgs mlp{};
   size_t dyn = 0;
   if (p.scorer == TAPS_SCORER_LEARNED) {
     const taps_scorer_mlp& w = *p.mlp;
     mlp = ScorerArgs{w.emb, w.W1, w.b1, w.w2, w.b2, w.root_token, w.emb_dim, w.hidden, p.vocab};
     dyn = (size_t)p.block * p.K * p.K * sizeof(double);
+  }
+  if (tables) {
+    const int rows = p.batch * p.block;
+    rtop = (uint64_t*)tables;
+    qtab = (double*)(rtop + (size_t)rows * p.K);
+    const RowLists lists{cand, zpart, spart, plan.chunks, p.K, p.kind, 0, p.beta, out.topk_idx,
+                         out.topk_val};
+    const size_t rows_dyn = learned_row_layout(p.block, p.K, mlp.d, mlp.h).bytes;
+    // more than 64 KB of LDS (13 KB of it static) is asked for explicitly
+    if (rows_dyn > 48 * 1024 &&
+        hipFuncSetAttribute((const void*)learned_rows_kernel,
+                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)rows_dyn) != hipSuccess)
+      return hipErrorInvalidValue;
+    learned_rows_kernel<<<dim3((unsigned)rows), dim3(kRowThreads), rows_dyn, s>>>(p.block, lists,
+                                                                                 mlp, rtop, qtab);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
   }
 #define TAPS_SEL_L(SL, LR)                                                                    \
   do {                                                                                        \
@@ -1324,13 +1531,14 @@ hipError_t launch_select(const void* /*marg*/, const taps_select_params& p, cons
       return hipErrorInvalidValue;                                                            \
     select_kernel<SL, LR><<<grid, block, dyn, s>>>(                                           \
         p.block, p.K, p.budget, p.kind, p.lambda1, p.lambda2, p.tau, p.beta, plan.chunks,     \
-        marginal, cand, zpart, spart, mlp, out.parent, out.token, out.depth, out.rank,        \
-        out.q_reach, out.n_nodes, out.topk_idx, out.topk_val);                                \
+        marginal, cand, zpart, spart, mlp, rtop, qtab, out.parent,      \
+        out.token, out.depth, out.rank, out.q_reach, out.n_nodes, out.topk_idx, out.topk_val);                                \
   } while (0)
 #define TAPS_SEL(SL)                                                                          \
   do {                                                                                        \
-    if (spart) TAPS_SEL_L(SL, true);                                                          \
-    else TAPS_SEL_L(SL, false);                                                               \
+    if (qtab) TAPS_SEL_L(SL, kTables);                                                       \
+    else if (spart) TAPS_SEL_L(SL, kInPlace);                                                \
+    else TAPS_SEL_L(SL, kOwnRows);                                                             \
   } while (0)
   static_assert(TAPS_MAX_BUDGET <= 8 * kWave, "at most eight frontier slots per lane");
   switch (slots) {
