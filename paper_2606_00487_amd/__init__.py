@@ -36,7 +36,9 @@ def _ptr(t: torch.Tensor | None) -> int | None:
 
 
 def _stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    # the handle itself: a torch.cuda.Stream object for each of a round's calls costs more
+    # than the rest of the call's arguments together
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _need(t: torch.Tensor, name: str, dtype, shape=None):
@@ -46,7 +48,7 @@ def _need(t: torch.Tensor, name: str, dtype, shape=None):
         raise TypeError(f"{name}: expected a GPU tensor")
     if not t.is_contiguous():
         raise ValueError(f"{name}: must be contiguous")
-    if shape is not None and tuple(t.shape) != tuple(shape):
+    if shape is not None and t.shape != shape:   # a torch.Size is a tuple
         raise ValueError(f"{name}: expected shape {tuple(shape)}, got {tuple(t.shape)}")
 
 
@@ -166,7 +168,7 @@ class TreeAttention:
         tdt = _TORCH_DT[dtype]
         _need(Q, "Q_tree", tdt, (batch, budget, Hq, hd))
         _need(K, "K_cache", tdt)
-        _need(V, "V_cache", tdt, tuple(K.shape))
+        _need(V, "V_cache", tdt, K.shape)
         if K.dim() != 3 or K.shape[1:] != (Hkv, hd):
             raise ValueError(f"K_cache: expected [rows, {Hkv}, {hd}], got {tuple(K.shape)}")
         _need(kv_offset, "kv_offset", torch.int64, (batch,))
@@ -211,7 +213,7 @@ class PagedTreeAttention:
         if K_pages.dim() != 4 or K_pages.shape[1:] != (self.page_rows, Hkv, hd):
             raise ValueError(f"K_pages: expected [pages, {self.page_rows}, {Hkv}, {hd}], "
                              f"got {tuple(K_pages.shape)}")
-        _need(V_pages, "V_pages", torch.bfloat16, tuple(K_pages.shape))
+        _need(V_pages, "V_pages", torch.bfloat16, K_pages.shape)
         _need(block_table, "block_table", torch.int32)
         if block_table.dim() != 2 or block_table.shape[0] != batch:
             raise ValueError(f"block_table: expected [{batch}, max_pages], "
@@ -268,7 +270,7 @@ class KVCommit:
         batch, budget, block, Hkv, hd, max_ctx, dtype = self.shape
         tdt = _TORCH_DT[dtype]
         _need(K, "K_cache", tdt)
-        _need(V, "V_cache", tdt, tuple(K.shape))
+        _need(V, "V_cache", tdt, K.shape)
         if K.dim() != 3 or K.shape[1:] != (Hkv, hd):
             raise ValueError(f"K_cache: expected [rows, {Hkv}, {hd}], got {tuple(K.shape)}")
         _need(kv_offset, "kv_offset", torch.int64, (batch,))
@@ -303,7 +305,7 @@ class PagedKVCommit:
         batch, budget, block, Hkv, hd, max_ctx, dtype = self.shape
         tdt = _TORCH_DT[dtype]
         _need(K_pages, "K_pages", tdt)
-        _need(V_pages, "V_pages", tdt, tuple(K_pages.shape))
+        _need(V_pages, "V_pages", tdt, K_pages.shape)
         if K_pages.dim() != 4 or K_pages.shape[1:] != (self.page_rows, Hkv, hd):
             raise ValueError(f"K_pages: expected [pages, {self.page_rows}, {Hkv}, {hd}], "
                              f"got {tuple(K_pages.shape)}")
@@ -370,7 +372,7 @@ class VerifyLayer:
         batch, budget, Hq, Hkv, hd, hidden, max_ctx = self.shape
         _need(X, "X", torch.bfloat16, (batch, budget, hidden))
         _need(K, "K_cache", torch.bfloat16)
-        _need(V, "V_cache", torch.bfloat16, tuple(K.shape))
+        _need(V, "V_cache", torch.bfloat16, K.shape)
         _need(kv_offset, "kv_offset", torch.int64, (batch,))
         _need(ctx_len, "ctx_len", torch.int32, (batch,))
         ws = w.struct()
@@ -409,7 +411,7 @@ class PagedVerifyLayer:
         if K_pages.dim() != 4 or K_pages.shape[1:] != (self.page_rows, Hkv, hd):
             raise ValueError(f"K_pages: expected [pages, {self.page_rows}, {Hkv}, {hd}], "
                              f"got {tuple(K_pages.shape)}")
-        _need(V_pages, "V_pages", torch.bfloat16, tuple(K_pages.shape))
+        _need(V_pages, "V_pages", torch.bfloat16, K_pages.shape)
         _need(block_table, "block_table", torch.int32)
         if block_table.dim() != 2 or block_table.shape[0] != batch:
             raise ValueError(f"block_table: expected [{batch}, max_pages], "
