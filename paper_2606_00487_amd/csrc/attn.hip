@@ -542,7 +542,7 @@ __global__ __launch_bounds__(256) void attn_bf16_w4_kernel(
     TAPS_WAIT_VMCNT(6 * LPH);         // V(i) and K(i+1) have landed (this wave's part)
     TAPS_STAGE_BARRIER();             // ... and every other wave's part
     softmax_pv(sc, v_cur, k_next, sn, k_begin + i * STEP);
-    TAPS_STAGE_BARRIER();             // the buffers of K(i+1) and V(i) may be refilled
+    TAPS_LDS_BARRIER();               // every wave has read K(i+1) and V(i): may be refilled
   };
 
   // ---- S(0), then the steps, unrolled by four so that every access names its buffer
@@ -553,7 +553,7 @@ __global__ __launch_bounds__(256) void attn_bf16_w4_kernel(
   for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
     for (int kk = 0; kk < NKK; ++kk) s_mfma(s_k0, kb, kk, sA);
-  TAPS_STAGE_BARRIER();               // every wave has read K(0): step 0 refills its buffer
+  TAPS_LDS_BARRIER();                 // every wave has read K(0): step 0 refills its buffer
   for (int i = 0;;) {
     step(sA, sB, s_k0, s_k1, s_v0, s_v3, i);
     if (++i >= nst) break;
