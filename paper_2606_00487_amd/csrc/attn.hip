@@ -272,7 +272,7 @@ __global__ __launch_bounds__(256) void attn_bf16_w4_kernel(
     const uint16_t* __restrict__ Vc, const int64_t* __restrict__ offp,
     const int32_t* __restrict__ ctxp, const int32_t* __restrict__ parentp,
     const int32_t* __restrict__ nnp, int N, int Hq, int Hkv, int max_ctx, float scale_log2,
-    int split_len, int splits, int mtiles, int pairs, int mrows_pad, uint16_t* __restrict__ wsO,
+    int split_len, int splits, int mtiles, int pairs, int mrows_pad, void* __restrict__ wsO,
     float2* __restrict__ wsML, int batch, int target_pairs, RaggedCost rc, int lcap,
     int2* __restrict__ tab) {
   // the body uses the buffer-resource type, which exists only in the device pass; the
@@ -571,17 +571,21 @@ __global__ __launch_bounds__(256) void attn_bf16_w4_kernel(
   const float lsum = l_run + other_half(l_run);
   const float inv = lsum > 0.f ? 1.f / lsum : 0.f;
 
-  // ---- write this split's partial: O / sum in bf16, reference max and sum
+  // ---- write this split's partial: O / sum (fp32 for the ragged list, else bf16),
+  // reference max and sum
   const size_t obase = (size_t)pair * mrows_pad;
   const int qr = row0 + rg * 32 + l32;
-  uint16_t* op = wsO + (obase + qr) * HD;
+  const size_t orow = (obase + qr) * HD;
 #pragma unroll
   for (int db = 0; db < NDB; ++db)
 #pragma unroll
     for (int r4 = 0; r4 < 4; ++r4) {
       const int d = db * 32 + 8 * r4 + 4 * hl;
-      *(uint2*)(op + d) = pack_bf16x4(o[db][4 * r4] * inv, o[db][4 * r4 + 1] * inv,
-                                      o[db][4 * r4 + 2] * inv, o[db][4 * r4 + 3] * inv);
+      float x[4];
+#pragma unroll
+      for (int t = 0; t < 4; ++t) x[t] = o[db][4 * r4 + t] * inv;
+      if (tab != nullptr) *(float4*)((float*)wsO + orow + d) = make_float4(x[0], x[1], x[2], x[3]);
+      else *(uint2*)((uint16_t*)wsO + orow + d) = pack_bf16x4(x[0], x[1], x[2], x[3]);
     }
   if (hl == 0) wsML[obase + qr] = make_float2(m_ref, lsum);
 #endif
@@ -674,7 +678,7 @@ __device__ __attribute__((always_inline)) inline void attn_bf16_body(
     const uint16_t* __restrict__ Vc, const int64_t* __restrict__ offp,
     const int32_t* __restrict__ ctxp, const int32_t* __restrict__ parentp,
     const int32_t* __restrict__ nnp, int N, int Hq, int Hkv, int max_ctx, float scale_log2,
-    int split_len, int splits, int mtiles, int pairs, int mrows_pad, uint16_t* __restrict__ wsO,
+    int split_len, int splits, int mtiles, int pairs, int mrows_pad, void* __restrict__ wsO,
     float2* __restrict__ wsML, DivMagic dm, int batch, int target_pairs, RaggedCost rc, int lcap,
     int2* __restrict__ tab, const PagedKV& pk) {
   constexpr int HD = 128;
@@ -1190,14 +1194,34 @@ __device__ __attribute__((always_inline)) inline void attn_bf16_body(
   const float Ls = lsum * a0 + ml.y * a1;
   const float inv = Ls > 0.f ? 1.f / Ls : 0.f;
 
-  // ---- write this split's partial: O / sum in bf16 for this group's 64 head dims of the
-  // wave's 32 rows, max and sum.  The tile goes through LDS (this wave's V slot, free
-  // now) so that each store instruction writes whole 128-byte row segments.  The stores
-  // are non-temporal: only the combine, a later launch, reads the partials, and streaming
-  // them out of the L2 leaves less to write back when the kernel ends (measured: the
-  // kernel took 0.5 us less at the Qwen3-8B shape).
+  // ---- write this split's partial: O / sum for this group's 64 head dims of the wave's 32
+  // rows (fp32 for the ragged list, else bf16), max and sum.  The tile goes through LDS (this
+  // wave's V slot, free now), 128 bytes of every row at a time: both head blocks in bf16, one
+  // in fp32.  So each store instruction writes whole 128-byte row segments.  The stores are
+  // non-temporal: only the combine, a later launch, reads the partials, and streaming them
+  // out of the L2 leaves less to write back when the kernel ends (measured: the kernel took
+  // 0.5 us less at the Qwen3-8B shape).
   constexpr int TROW = 144;            // bytes per staged row (128 + 16: fewer bank conflicts)
   unsigned char* const stage = s_v + wave * TILEB;
+  const size_t obase = (size_t)pair * mrows_pad;
+  const int qbase = row0 + rg * 32;
+  auto wave_sync = []() __attribute__((always_inline)) {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  };
+  // the staged 128 bytes of every row to byte `at` of the rows' partials of `rowb` bytes
+  auto flush = [&](int rowb, int at) __attribute__((always_inline)) {
+    wave_sync();
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int r = 8 * i + (lane >> 3), c = (lane & 7) * 16;   // row in the tile, byte in it
+      const i32x4 v = *(const i32x4*)(stage + r * TROW + c);
+      __builtin_nontemporal_store(
+          v, (i32x4*)((unsigned char*)wsO + (obase + qbase + r) * rowb + at + c));
+    }
+    wave_sync();
+  };
 #pragma unroll
   for (int j = 0; j < 2; ++j) {
     const f32x16 lo = o[j], hi = o[2 + j];
@@ -1209,20 +1233,15 @@ __device__ __attribute__((always_inline)) inline void attn_bf16_body(
       float x[4];
 #pragma unroll
       for (int t = 0; t < 4; ++t) x[t] = (own[4 * r4 + t] * a0 + tv[t] * a1) * inv;
-      *(uint2*)(stage + l32 * TROW + 2 * (j * 32 + 8 * r4 + 4 * hl)) = pack_bf16x4(x[0], x[1], x[2], x[3]);
+      const int d = 8 * r4 + 4 * hl;
+      if (tab != nullptr)
+        *(float4*)(stage + l32 * TROW + 4 * d) = make_float4(x[0], x[1], x[2], x[3]);
+      else
+        *(uint2*)(stage + l32 * TROW + 2 * (j * 32 + d)) = pack_bf16x4(x[0], x[1], x[2], x[3]);
     }
+    if (tab != nullptr) flush(HD * 4, kg * 256 + j * 128);
   }
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  const size_t obase = (size_t)pair * mrows_pad;
-  const int qbase = row0 + rg * 32;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int r = 8 * i + (lane >> 3), c = (lane & 7) * 16;   // row in the tile, byte in the half
-    const i32x4 v = *(const i32x4*)(stage + r * TROW + c);
-    __builtin_nontemporal_store(v, (i32x4*)((unsigned char*)(wsO + (obase + qbase + r) * HD) + kg * 128 + c));
-  }
+  if (tab == nullptr) flush(HD * 2, kg * 128);
   const int qr = qbase + l32;
   if (kg == 0 && hl == 0) {
     f32x2 ml2;
@@ -1240,7 +1259,7 @@ __global__ __launch_bounds__(512) void attn_bf16_kernel(
     const uint16_t* __restrict__ Vc, const int64_t* __restrict__ offp,
     const int32_t* __restrict__ ctxp, const int32_t* __restrict__ parentp,
     const int32_t* __restrict__ nnp, int N, int Hq, int Hkv, int max_ctx, float scale_log2,
-    int split_len, int splits, int mtiles, int pairs, int mrows_pad, uint16_t* __restrict__ wsO,
+    int split_len, int splits, int mtiles, int pairs, int mrows_pad, void* __restrict__ wsO,
     float2* __restrict__ wsML, DivMagic dm, int batch, int target_pairs, RaggedCost rc, int lcap,
     int2* __restrict__ tab) {
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -1256,7 +1275,7 @@ __global__ __launch_bounds__(512) void attn_bf16_paged_kernel(
     const uint16_t* __restrict__ Vc, const int64_t* __restrict__ offp,
     const int32_t* __restrict__ ctxp, const int32_t* __restrict__ parentp,
     const int32_t* __restrict__ nnp, int N, int Hq, int Hkv, int max_ctx, float scale_log2,
-    int split_len, int splits, int mtiles, int pairs, int mrows_pad, uint16_t* __restrict__ wsO,
+    int split_len, int splits, int mtiles, int pairs, int mrows_pad, void* __restrict__ wsO,
     float2* __restrict__ wsML, DivMagic dm, int batch, int target_pairs, RaggedCost rc, int lcap,
     int2* __restrict__ tab, PagedKV pk) {
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -1273,9 +1292,9 @@ __global__ __launch_bounds__(512) void attn_bf16_paged_kernel(
 // spread over 256 workgroups, one per CU, and each CU pulls half as many partials (the
 // combine took 4.7 us against 5.0 us with 256 threads).
 constexpr int kCombineThreads = 128;
-template <int HD, int CH>
+template <int HD, int CH, bool RAGGED>
 __global__ __launch_bounds__(kCombineThreads) void attn_combine_kernel(
-    const uint16_t* __restrict__ wsO, const float2* __restrict__ wsML,
+    const void* __restrict__ wsO, const float2* __restrict__ wsML,
     const int32_t* __restrict__ ctxp, const int32_t* __restrict__ nnp, int N, int Hq, int Hkv,
     int max_ctx, int split_len, int splits, int mrows_pad, DivMagic dm,
     uint16_t* __restrict__ O, const int2* __restrict__ tab, int batch) {
@@ -1295,7 +1314,7 @@ __global__ __launch_bounds__(kCombineThreads) void attn_combine_kernel(
   // table, written by the attention kernel, or the host's fixed split count)
   size_t base;
   int cap;
-  if (tab != nullptr) {
+  if constexpr (RAGGED) {
     const int2 t = tab[b];
     base = (size_t)t.x + (size_t)g * t.y;
     cap = t.y;
@@ -1304,19 +1323,23 @@ __global__ __launch_bounds__(kCombineThreads) void attn_combine_kernel(
     base = (size_t)(b * Hkv + g) * splits;
     cap = splits;
   }
-  // each split holds O_s / l_s (bf16) and (m_s, l_s) with m_s in base 2:
+  // each split holds O_s / l_s (fp32 for the ragged list, else bf16) and (m_s, l_s) with m_s
+  // in base 2:
   // O = sum_s 2^(m_s - M) l_s (O_s / l_s) / sum_s 2^(m_s - M) l_s.  The loads of the first
   // CH splits go out before the request's sizes are known (their addresses do not depend on
   // them; splits past the request's keys are masked once the sizes have arrived), then
   // groups of up to CH splits are merged with a running maximum.
+  constexpr int NV = RAGGED ? 2 : 1;   // 16-byte loads of the 8 values
   float2 ml[CH];
-  uint4 ov[CH];
+  uint4 ov[CH][NV];
   auto load_group = [&](int s0) __attribute__((always_inline)) {
 #pragma unroll
     for (int t = 0; t < CH; ++t) {
       const size_t r = (base + min(s0 + t, cap - 1)) * mrows_pad + qr;
       ml[t] = wsML[r];
-      ov[t] = *(const uint4*)(wsO + r * HD + d);
+#pragma unroll
+      for (int v = 0; v < NV; ++v)
+        ov[t][v] = *(const uint4*)((const unsigned char*)wsO + (r * HD + d) * (2 * NV) + 16 * v);
     }
   };
   if (cap > 0) load_group(0);
@@ -1338,7 +1361,8 @@ __global__ __launch_bounds__(kCombineThreads) void attn_combine_kernel(
     for (int t = 0; t < CH; ++t)
       if (s0 + t >= nspl) {
         ml[t] = make_float2(-INFINITY, 0.f);
-        ov[t] = make_uint4(0u, 0u, 0u, 0u);
+#pragma unroll
+        for (int v = 0; v < NV; ++v) ov[t][v] = make_uint4(0u, 0u, 0u, 0u);
       }
     float Mc = M;
 #pragma unroll
@@ -1352,11 +1376,18 @@ __global__ __launch_bounds__(kCombineThreads) void attn_combine_kernel(
     for (int t = 0; t < CH; ++t) {
       const float w = ml[t].x == -INFINITY ? 0.f : exp2f(ml[t].x - Mc) * ml[t].y;
       L += w;
-      const uint32_t wd[4] = {ov[t].x, ov[t].y, ov[t].z, ov[t].w};
 #pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        acc[2 * k] += w * __uint_as_float(wd[k] << 16);
-        acc[2 * k + 1] += w * __uint_as_float(wd[k] & 0xFFFF0000u);
+      for (int v = 0; v < NV; ++v) {
+        const uint32_t wd[4] = {ov[t][v].x, ov[t][v].y, ov[t][v].z, ov[t][v].w};
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          if constexpr (RAGGED) {
+            acc[4 * v + k] += w * __uint_as_float(wd[k]);
+          } else {
+            acc[2 * k] += w * __uint_as_float(wd[k] << 16);
+            acc[2 * k + 1] += w * __uint_as_float(wd[k] & 0xFFFF0000u);
+          }
+        }
       }
     }
     M = Mc;
@@ -1436,15 +1467,20 @@ AttnPlan plan_attn(int batch, int budget, int Hq, int Hkv, int head_dim, int max
   return p;
 }
 
-// split partials [slot][mtiles * mtile][head_dim] bf16, then their (max, sum) pairs, then
-// (ragged list) the per-request table of the combine
+// split partials [slot][mtiles * mtile][head_dim], then their (max, sum) pairs, then (ragged
+// list) the per-request table of the combine.  The ragged list's partials are fp32: its split
+// lengths follow the batch, and a partial rounded to bf16 would give a request cut in two a
+// quarter more error than the same request uncut (2.9e-3 against 2.3e-3 of the result).  The
+// wider partials cost 9 us of 207 at 16 requests of 512-16K keys (32/8 heads of 128), 0.5 of
+// 28.8 at 4 of 2-8K with head_dim 64, 5 of 548 at 4 x 32K keys.
+static size_t attn_part_bytes(const AttnPlan& pl) { return pl.ragged ? 4 : 2; }
 static size_t attn_rows(const AttnPlan& pl, int batch, int Hkv) {
   const size_t slots = pl.ragged ? (size_t)pl.pairs_max : (size_t)batch * Hkv * pl.splits;
   return slots * (size_t)pl.mtiles * pl.mtile;
 }
 static size_t attn_tab_offset(const AttnPlan& pl, int batch, int Hkv, int head_dim) {
   const size_t rows = attn_rows(pl, batch, Hkv);
-  return (rows * head_dim * sizeof(uint16_t) + rows * sizeof(float2) + 15) & ~(size_t)15;
+  return (rows * head_dim * attn_part_bytes(pl) + rows * sizeof(float2) + 15) & ~(size_t)15;
 }
 
 size_t attn_ws_bytes(const AttnPlan& pl, int batch, int /*budget*/, int /*Hq*/, int Hkv,
@@ -1466,8 +1502,8 @@ static hipError_t launch_attn_bf16_impl(const void* Q, const void* K, const void
   if (batch <= 0) return hipSuccess;
   const int mrows_pad = pl.mtiles * pl.mtile;
   const size_t rows = attn_rows(pl, batch, Hkv);
-  uint16_t* wsO = (uint16_t*)ws;
-  float2* wsML = (float2*)((char*)ws + rows * head_dim * sizeof(uint16_t));
+  void* wsO = ws;
+  float2* wsML = (float2*)((char*)ws + rows * head_dim * attn_part_bytes(pl));
   int2* tab = pl.ragged ? (int2*)((char*)ws + attn_tab_offset(pl, batch, Hkv, head_dim)) : nullptr;
   const int pairs = pl.ragged ? pl.pairs_max : pl.splits * batch * Hkv;
   dim3 grid((unsigned)(8 * pl.mtiles * ((pairs + 7) / 8)));
@@ -1521,9 +1557,9 @@ static hipError_t launch_attn_bf16_impl(const void* Q, const void* K, const void
   const DivMagic cm{0u, 0u, DivMagic::make(Hq), DivMagic::make(Hq / Hkv)};
   // splits per group: the one-request plan's split count (rounded up to 4, 8 or 16), 4
   // for the ragged list
-  const int ch = tab != nullptr || pl.splits <= 4 ? 4 : pl.splits <= 8 ? 8 : 16;
-#define TAPS_COMBINE(HDC, CHC)                                                               \
-  attn_combine_kernel<HDC, CHC>                                                              \
+  const int ch = pl.splits <= 4 ? 4 : pl.splits <= 8 ? 8 : 16;
+#define TAPS_COMBINE(HDC, CHC, RG)                                                           \
+  attn_combine_kernel<HDC, CHC, RG>                                                          \
       <<<dim3((unsigned)((rows_req + kCombineThreads / (HDC / 8) - 1) /                      \
                          (kCombineThreads / (HDC / 8))),                                      \
               (unsigned)batch),                                                              \
@@ -1531,13 +1567,15 @@ static hipError_t launch_attn_bf16_impl(const void* Q, const void* K, const void
                                         pl.split_len, pl.splits, mrows_pad, cm, (uint16_t*)O, \
                                         tab, batch)
   if (head_dim == 128) {
-    if (ch == 4) TAPS_COMBINE(128, 4);
-    else if (ch == 8) TAPS_COMBINE(128, 8);
-    else TAPS_COMBINE(128, 16);
+    if (tab != nullptr) TAPS_COMBINE(128, 4, true);
+    else if (ch == 4) TAPS_COMBINE(128, 4, false);
+    else if (ch == 8) TAPS_COMBINE(128, 8, false);
+    else TAPS_COMBINE(128, 16, false);
   } else {
-    if (ch == 4) TAPS_COMBINE(64, 4);
-    else if (ch == 8) TAPS_COMBINE(64, 8);
-    else TAPS_COMBINE(64, 16);
+    if (tab != nullptr) TAPS_COMBINE(64, 4, true);
+    else if (ch == 4) TAPS_COMBINE(64, 4, false);
+    else if (ch == 8) TAPS_COMBINE(64, 8, false);
+    else TAPS_COMBINE(64, 16, false);
   }
 #undef TAPS_COMBINE
   return hipGetLastError();
