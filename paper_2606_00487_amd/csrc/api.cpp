@@ -13,6 +13,11 @@ constexpr int kMaxChunks = 64;  // per-row chunk lists the selection kernel merg
 
 bool finite(double x) { return std::isfinite(x); }
 
+bool needs_z(const taps_select_params* p) {
+  return (p->scorer == TAPS_SCORER_MARGINAL && p->kind == TAPS_LOGITS) ||
+         p->scorer == TAPS_SCORER_LEARNED;
+}
+
 taps_status select_check(const taps_select_params* p) {
   if (!p) return TAPS_ERR_INVALID_ARG;
   if (p->batch < 0) return TAPS_ERR_INVALID_ARG;
@@ -45,14 +50,10 @@ taps_status select_check(const taps_select_params* p) {
   }
   const int64_t rows = (int64_t)p->batch * p->block;
   if (rows > (int64_t)1 << 20) return TAPS_ERR_UNSUPPORTED;
-  const TopkPlan plan = plan_topk(p->vocab, (int)rows > 0 ? (int)rows : 1, p->dtype);
+  const TopkPlan plan = plan_topk(p->vocab, (int)rows > 0 ? (int)rows : 1, p->dtype,
+                                  needs_z(p));
   if (plan.chunks > kMaxChunks) return TAPS_ERR_UNSUPPORTED;
   return TAPS_OK;
-}
-
-bool needs_z(const taps_select_params* p) {
-  return (p->scorer == TAPS_SCORER_MARGINAL && p->kind == TAPS_LOGITS) ||
-         p->scorer == TAPS_SCORER_LEARNED;
 }
 
 taps_status attn_check(int32_t batch, int32_t budget, int32_t Hq, int32_t Hkv, int32_t hd,
@@ -127,7 +128,7 @@ taps_status taps_select_validate(const taps_select_params* p) { return select_ch
 size_t taps_select_workspace_bytes(const taps_select_params* p) {
   if (select_check(p) != TAPS_OK || p->batch == 0) return 0;
   const int rows = p->batch * p->block;
-  const TopkPlan plan = plan_topk(p->vocab, rows, p->dtype);
+  const TopkPlan plan = plan_topk(p->vocab, rows, p->dtype, needs_z(p));
   const size_t cand = (size_t)rows * plan.chunks * p->K * sizeof(uint64_t);
   const size_t part = (size_t)rows * plan.chunks * kZSub * sizeof(int64_t);
   return cand + (needs_z(p) ? part : 0) + (p->scorer == TAPS_SCORER_LEARNED ? part : 0);
@@ -150,7 +151,7 @@ taps_status taps_select(const void* marginals, const taps_select_params* p, cons
   const size_t need = taps_select_workspace_bytes(p);
   if (!ws || ws_bytes < need || ((uintptr_t)ws & 7) != 0) return TAPS_ERR_WORKSPACE;
   const int rows = p->batch * p->block;
-  const TopkPlan plan = plan_topk(p->vocab, rows, p->dtype);
+  const TopkPlan plan = plan_topk(p->vocab, rows, p->dtype, needs_z(p));
   if (launch_topk_chunks(marginals, p->dtype, rows, p->vocab, p->K, plan, (uint64_t*)ws,
                          stream) != hipSuccess)
     return TAPS_ERR_HIP;

@@ -32,7 +32,8 @@ struct TopkPlan {
   int chunks;      // chunks per row
   int per_thread;  // elements per thread (chunk_len / 256)
 };
-TopkPlan plan_topk(int vocab, int rows, int dtype);
+// z: the rows' full-vocabulary sums are taken too (launch_marginal_z)
+TopkPlan plan_topk(int vocab, int rows, int dtype, bool z);
 
 hipError_t launch_topk_chunks(const void* marg, int dtype, int rows, int vocab, int K,
                               const TopkPlan& plan, uint64_t* cand, hipStream_t s);
