@@ -189,7 +189,7 @@ taps_status taps_select_noalloc(const void *marginals, const taps_select_params 
 
 /* Bytes of scratch tree_verify_attn needs (split-KV partial outputs).  TAPS_FP32 calls use
  * this much to split long contexts (0 for short ones) and also run with less or none, more
- * slowly. */
+ * slowly.  Calls that may overlap on the GPU need scratch of their own. */
 size_t tree_verify_attn_workspace_bytes(int32_t batch, int32_t budget, int32_t Hq,
                                         int32_t Hkv, int32_t head_dim, int32_t max_ctx,
                                         int32_t dtype);

@@ -160,10 +160,12 @@ class TreeAttention:
         self.ws_bytes = self.lib.tree_verify_attn_workspace_bytes(batch, budget, Hq, Hkv,
                                                                   head_dim, max_ctx, dtype)
         self.ws = torch.empty(max(self.ws_bytes, 16), dtype=torch.uint8, device=device)
+        self._home = _stream() if self.ws.is_cuda else None   # the stream whose calls share ws
 
     def __call__(self, Q, K, V, kv_offset, ctx_len, parent, n_nodes, out=None, events=None):
         """events: optional (begin, end) torch.cuda.Event pair recorded around the main
         attention kernel only (tree_verify_attn_timed)."""
+        stream, ws = _stream(), self.ws
         batch, budget, Hq, Hkv, hd, max_ctx, dtype = self.shape
         tdt = _TORCH_DT[dtype]
         _need(Q, "Q_tree", tdt, (batch, budget, Hq, hd))
@@ -177,9 +179,12 @@ class TreeAttention:
         _need(n_nodes, "n_nodes", torch.int32, (batch,))
         O = out if out is not None else torch.empty_like(Q)
         _need(O, "O", tdt, (batch, budget, Hq, hd))
+        if dtype == FP32 and self.ws_bytes and stream != self._home:
+            # fp32 calls of one object may overlap on several streams: scratch of their own
+            ws = torch.empty(self.ws_bytes, dtype=torch.uint8, device=Q.device)
         args = (_ptr(Q), _ptr(K), _ptr(V), _ptr(kv_offset), _ptr(ctx_len), _ptr(parent),
                 _ptr(n_nodes), batch, budget, Hq, Hkv, hd, max_ctx, dtype, self.scale, _ptr(O),
-                _ptr(self.ws), self.ws_bytes, _stream())
+                _ptr(ws), self.ws_bytes, stream)
         if events is None:
             _lib.check(self.lib, "tree_verify_attn", self.lib.tree_verify_attn(*args))
         else:
