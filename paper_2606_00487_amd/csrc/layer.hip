@@ -684,6 +684,9 @@ GemmPlan plan_gemm(int M, int N, int K, bool head_cols) {
                                     0.21 * nb / (double)((M + 63) / 64));
       consider(GemmPlan{sp, 32 * nb, 64}, (double)((wgs + 255) / 256) * (S * stage + 3.0));
     }
+    // a tile's 256 rows of X (and its 128 weight rows) must span less than the 2^32 bytes of a
+    // buffer resource: output projections of up to 65535 heads (64 rows: four times as many)
+    if ((long long)K * 2 * 256 >= (1ll << 32)) continue;
     const TileGrid g = tile_grid(M, N, sp);
     const double half = std::max(0.70, 0.84 / (double)((M + 127) / 128));
     consider(GemmPlan{sp, 128, 256}, (double)((g.full + 255) / 256) * (S * 0.94 + 4.0) +

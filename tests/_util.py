@@ -1,6 +1,8 @@
 """Helpers shared by the GPU tests: upload seeded inputs, run the oracle, compare."""
 from __future__ import annotations
 
+import ctypes
+
 import numpy as np
 import torch
 
@@ -225,3 +227,26 @@ def attention_error(got: np.ndarray, ref: np.ndarray, dtype: int, label: str = "
     assert mabs <= ta, f"{label}: max-abs {mabs:.3e} > {ta}"
     assert mrel <= tr, f"{label}: max-rel {mrel:.3e} > {tr}"
     return mabs, mrel, hist
+
+
+class GemmPlan(ctypes.Structure):
+    """The projections' plan: K splits, output columns and rows per workgroup."""
+    _fields_ = [("splits", ctypes.c_int), ("cols", ctypes.c_int), ("rows", ctypes.c_int)]
+
+    @property
+    def fused(self) -> bool:
+        return self.rows > 64 and self.splits == 1
+
+
+def gemm_plan(M: int, N: int, K: int, head_cols: bool) -> GemmPlan:
+    """taps::plan_gemm of the library (a host function; C++ name as compiled)."""
+    from paper_2606_00487_amd import _lib
+    f = _lib.load()._ZN4taps9plan_gemmEiiib
+    f.restype, f.argtypes = GemmPlan, [ctypes.c_int] * 3 + [ctypes.c_bool]
+    return f(M, N, K, head_cols)
+
+
+def layer_plans(B: int, N: int, hidden: int, Hq: int, Hkv: int) -> tuple[GemmPlan, GemmPlan]:
+    """The Q/K/V and the output projection's plans of a layer call."""
+    return (gemm_plan(B * N, (Hq + 2 * Hkv) * 128, hidden, True),
+            gemm_plan(B * N, hidden, Hq * 128, False))
