@@ -133,17 +133,17 @@ def test_layer_ragged_rows_span_several_tiles(taps):
 
 
 def test_layer_many_rows_take_the_widest_gemm_tiles(taps):
-    """M = 8 x 128 = 1024 rows: the Q/K/V projection's plan takes 128 columns per workgroup
-    and one K split (the fewest rounds of workgroups), the output projection 64 columns and
-    eight splits; ragged node counts, empty and short contexts."""
+    """M = 8 x 128 = 1024 rows: the Q/K/V projection's plan takes the widest tiles (256 and 128
+    rows by 128 columns) and one K split with the epilogue in the GEMM, the output projection
+    64 rows, 64 columns and four splits; ragged node counts, empty and short contexts."""
     _run(taps, np.random.default_rng(6), B=8, N=128, H=128, Hq=8, Hkv=4,
          ctx=[30, 0, 65, 3, 100, 7, 12, 50], n=[128, 1, 77, 128, 5, 64, 100, 33])
 
 
-def test_layer_many_pairs_take_four_heads_per_wave(taps):
-    """M = 8 x 128 rows and 12 heads per node (8 query, 2 key, 2 value): the rotary pass
-    gives each wave four heads of a node (the last group of the node's three partly
-    filled: heads 8-11 of one workgroup of 16)."""
+def test_layer_many_pairs_of_node_and_head(taps):
+    """M = 8 x 128 rows and 12 heads per node (8 query, 2 key, 2 value): the same tiles with
+    two KV heads (the rotary pass of four heads per wave, which so many pairs took before the
+    tiles, has cases of its own in test_gpu_layer_tiles.py)."""
     _run(taps, np.random.default_rng(7), B=8, N=128, H=128, Hq=8, Hkv=2,
          ctx=[0, 41, 9, 130, 1, 64, 7, 20], n=[128, 128, 3, 90, 1, 60, 128, 17])
 

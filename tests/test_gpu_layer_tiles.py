@@ -1,38 +1,74 @@
-"""GPU parity of the verification layer where its projections run in tiles of 256 and 128 rows
-with the epilogue in the GEMM: ragged last tiles, a hidden size that is no multiple of 128, a
-split of the grid into both tile heights, nodes past n_nodes, and the paged stores."""
+"""GPU parity of the verification layer over the kernels that its projections' plans choose
+from: tiles of 256 and 128 rows with the epilogue in the GEMM (ragged last tiles, a hidden size
+that is no multiple of 128, a split of the grid into both tile heights, nodes past n_nodes, the
+paged stores), the same tiles with K splits, and 64-row workgroups of every width with the
+rotary pass of one and of four heads per wave.  Every case asserts the plan it is there for."""
 import numpy as np
 import pytest
 import torch
 
+from tests._util import layer_plans
 from tests.test_gpu_layer import _run, taps  # noqa: F401
+from tests.test_gpu_paged import _run_layer_paged
 from workloads import kv_offsets
 
 pytestmark = pytest.mark.gpu
 
 
-def _fused(taps, B, N, H, Hq, Hkv, max_ctx):
-    """Both projections fused: the scratch holds only the rotations besides Q, O and the
-    attention's."""
-    lib = taps.load()
-    al = lambda x: (x + 255) & ~255
-    rest = 2 * al(B * N * Hq * 256) + al(
-        lib.tree_verify_attn_workspace_bytes(B, N, Hq, Hkv, 128, max_ctx, 0))
-    return lib.verify_layer_workspace_bytes(B, N, Hq, Hkv, 128, H, max_ctx) - rest == al(B * N * 512)
+def _plans(B, N, H, Hq, Hkv):
+    """(K splits, output columns and rows per workgroup) of the Q/K/V and output projections."""
+    return tuple((p.splits, p.cols, p.rows) for p in layer_plans(B, N, H, Hq, Hkv))
 
 
-@pytest.mark.parametrize("B,N,H,Hq,Hkv,both", [
-    (5, 420, 832, 8, 4, True),       # 256-row tiles, the last of 52 rows; 64 columns left over
-    (3, 300, 192, 16, 8, False),     # 128-row tiles, the last of 4 rows
-    (5, 420, 192, 20, 5, False),     # 256 tiles of 256 rows, the others of 128
+TILES = (1, 128, 256)   # 256- and 128-row tiles, the epilogue in the GEMM
+
+
+@pytest.mark.parametrize("B,N,H,Hq,Hkv,oproj", [
+    (5, 420, 832, 8, 4, TILES),          # 256-row tiles, the last of 52 rows; 64 columns left over
+    (3, 300, 192, 16, 8, (4, 64, 64)),   # 128-row tiles, the last of 4 rows
+    (5, 420, 192, 20, 5, (2, 64, 64)),   # 256 tiles of 256 rows, the others of 128
 ])
-def test_layer_tiles(taps, B, N, H, Hq, Hkv, both):  # noqa: F811
+def test_layer_tiles(taps, B, N, H, Hq, Hkv, oproj):  # noqa: F811
     rng = np.random.default_rng(N + H)
     ctx = [int(rng.integers(0, 40)) for _ in range(B)]
     n = [N, N - 1, 1, 0, N][:B]
-    assert _fused(taps, B, N, H, Hq, Hkv, max(ctx)) or not both
+    assert _plans(B, N, H, Hq, Hkv) == (TILES, oproj)
     _run(taps, rng, B, N, H, Hq, Hkv, ctx, n,
          sample_nodes=lambda b: sorted({0, n[b] // 2, max(0, n[b] - 1)} & set(range(n[b]))))
+
+
+# the plans that write fp32 partials, Q/K/V projection first; heads: of the rotary pass per wave
+# (four from 8192 (node, head) pairs on, the last group of 10 heads partly filled)
+SPLIT = [
+    (4, 99, 1216, 16, 4, (1, 96, 64), (4, 128, 256), 4),    # tiles, output projection
+    (4, 99, 2560, 12, 4, (4, 128, 256), (1, 128, 64), 1),   # tiles, Q/K/V projection
+    (13, 64, 2560, 6, 2, (4, 128, 256), TILES, 4),
+    (13, 64, 192, 6, 2, (1, 128, 64), (4, 64, 64), 4),      # 128 columns and 64 rows
+    (2, 40, 1216, 12, 4, (4, 128, 64), (4, 64, 64), 1),
+    (2, 40, 640, 40, 8, (1, 64, 64), (16, 128, 64), 1),
+]
+
+
+def _split_case(B, N, H, Hq, Hkv, qkv, oproj, heads):
+    assert _plans(B, N, H, Hq, Hkv) == (qkv, oproj)
+    assert (4 if B * N * (Hq + 2 * Hkv) > 8192 else 1) == heads
+    rng = np.random.default_rng(B + H)
+    ctx = [int(rng.integers(0, 70)) for _ in range(B)]
+    n = [[N, N - 3, 1, 0, N // 2][b % 5] for b in range(B)]
+    pick = lambda b: sorted({0, n[b] // 3, max(0, n[b] - 1)} & set(range(n[b])))
+    return rng, ctx, n, pick
+
+
+@pytest.mark.parametrize("case", SPLIT, ids=lambda c: "x".join(map(str, c[:5])))
+def test_layer_plans(taps, case):  # noqa: F811
+    rng, ctx, n, pick = _split_case(*case)
+    _run(taps, rng, *case[:5], ctx, n, sample_nodes=pick)
+
+
+@pytest.mark.parametrize("case", SPLIT[:4], ids=lambda c: "x".join(map(str, c[:5])))
+def test_layer_plans_paged(taps, case):  # noqa: F811
+    rng, ctx, n, pick = _split_case(*case)
+    _run_layer_paged(taps, rng, *case[:5], ctx, n, 32, sample_nodes=pick)
 
 
 def test_layer_tiles_paged(taps):  # noqa: F811
