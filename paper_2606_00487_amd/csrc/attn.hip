@@ -145,26 +145,37 @@ __device__ inline int wave_max_nonneg(int v) {
 // S_b = ceil(R_b / L) splits per KV head; its pairs are numbered from the prefix sum E_b of
 // Hkv * S_b, KV head by KV head.  When the lengths are close (the longest at most 5/4 of
 // the mean), L is the host's split length for max_ctx + budget keys, as in the one-request
-// plan.  Otherwise L is the one of 64 candidate lengths (one per lane, sized for 1/64 ..
-// 64/64 of target_pairs pairs) with the least estimated time for the batch's actual
-// lengths, or for more than 64 requests the one sized for 3/4 of target_pairs.  Every wave
-// of the workgroup computes the same result; wave 0 of the designated workgroup also writes
-// tab[b] = (E_b, S_b) and tab[batch] = (L, total pairs) for the split combine.
+// plan.  Otherwise L is the one of 64 candidate lengths (one per lane: equal parts of the
+// longest request, and lengths for 1/32 .. 32/32 of target_pairs pairs) with the least
+// estimated time for the batch's actual lengths, or for more than 64 requests the one sized
+// for 3/4 of target_pairs.  Every wave of the workgroup computes the same result; wave 0 of
+// the designated workgroup also writes tab[b] = (E_b, S_b) and tab[batch] = (L, total pairs)
+// for the split combine.
 //
-// The estimate, in 64-key steps, with `resident` workgroups at a time and `fixed` steps'
-// worth of prologue and partial writes in each: one workgroup takes L / 64 + fixed; a list
-// that fits the chip takes that long, a longer one the lesser of its full rounds and of the
-// mean load plus half a workgroup (the lists end in splits of all lengths).
+// The estimate, in 64-key steps.  The pairs go to the XCDs in turn, so the fullest XCD has
+// ceil(pairs / 8) of them, each of mtiles workgroups, for its 32 CUs; one workgroup takes
+// L / 64 steps and `fixed` for its prologue and partial writes.  What fits takes that long,
+// more takes the lesser of the XCD's full rounds and of its mean load plus `tail` of a
+// workgroup; the combine takes `part` for each split of the longest request.  Counting the
+// workgroups of the whole chip instead, 6 requests of 16-28K keys (16/2 heads of 128, 69
+// nodes) got 270 workgroups, of which an XCD had 35: 144 us with the combine, where 210
+// workgroups take 99.  The constants are those with the least mean loss, 2 %, against the
+// best length of 41 batches that were swept over their lengths.  (Two workgroups of the
+// head_dim 64 kernel fit a CU, but the softmax bounds both: counting on 64 fitted worse.)
 struct RaggedCost {
-  int resident, fixed;
+  float fixed, tail, part;
 };
+constexpr float kXcdCus = 32.f;
+__host__ __device__ constexpr RaggedCost ragged_cost(int head_dim) {
+  return head_dim == 128 ? RaggedCost{16.f, 1.f, 1.2f} : RaggedCost{4.f, 0.75f, 0.5f};
+}
 struct RaggedPick {
   int b, g, split, L;
   bool found;
 };
 __device__ inline RaggedPick ragged_pick(const int32_t* ctxp, const int32_t* nnp, int batch,
                                          int N, int max_ctx, int Hkv, int mtiles,
-                                         int target_pairs, RaggedCost rc, int lcap, int L_host,
+                                         int target_pairs, const RaggedCost rc, int lcap, int L_host,
                                          int p, int2* tab, bool write_tab) {
   const int lane = threadIdx.x & 63;
   long long tot = 0;
@@ -186,35 +197,34 @@ __device__ inline RaggedPick ragged_pick(const int32_t* ctxp, const int32_t* nnp
     tot = wave_sum_i64(tot);
   }
   rmax = wave_max_nonneg(rmax);
-  // splits of 128 keys that all fit the chip at once: nothing is shorter.  The search below
-  // costs ~0.8 us, which shows in such batches: 2 requests of 500 and 1100 keys, attention
-  // and combine against a length fixed by the host, 4 % more time with it, 1 % less without
-  int s128 = rc.resident + 1;
-  if (batch <= 64)
-    s128 = __builtin_amdgcn_readlane(wave_inclusive_sum((r_first + 127) >> 7), 63);
   int L;
   if (4ll * rmax * batch <= 5ll * tot) {
     L = L_host;
-  } else if ((long long)s128 * (Hkv * mtiles) <= rc.resident) {
-    L = min(lcap, 128);
   } else {
-    // the candidate's length: at least the exact quotient up to fp32 rounding, which adds
-    // less than one pair in target_pairs, so the pair count stays within target_pairs +
+    // the candidate's length: for target_pairs pairs at least the exact quotient up to fp32
+    // rounding, which adds less than one pair, so the pair count stays within target_pairs +
     // batch * Hkv
-    const int T = batch > 64 ? max(1, target_pairs * 3 / 4) : max(1, (target_pairs * (lane + 1)) >> 6);
     const float keys = (float)(tot * Hkv);
-    const float want = fminf(ceilf(keys / (float)T), (float)lcap);
-    L = min(lcap, max(128, ((int)want + 63) / 64 * 64));
+    const int T = batch > 64 ? max(1, target_pairs * 3 / 4)
+                             : max(1, (target_pairs * ((lane & 31) + 1)) >> 5);
+    float want = ceilf(keys / (float)T);
+    if (batch <= 64 && lane < 32)
+      want = fmaxf(ceilf((float)rmax / (float)(lane + 1)), ceilf(keys / (float)target_pairs));
+    L = min(lcap, max(128, ((int)fminf(want, (float)lcap) + 63) / 64 * 64));
     if (batch <= 64) {   // uniform
       const float inv = 1.f / (float)L;
       float s = 0.f;
       for (int b = 0; b < batch; ++b)
         s += ceilf((float)__builtin_amdgcn_readlane(r_first, b) * inv - 1e-4f);
-      const float wgs = s * (float)(Hkv * mtiles), res = (float)rc.resident;
-      const float one = (float)(L / 64 + rc.fixed);
-      const float mean = (keys * (float)mtiles * (1.f / 64.f) + wgs * (float)rc.fixed) / res;
-      const float cost =
-          wgs <= res ? one : fminf(ceilf(wgs / res) * one, mean + 0.5f * one);
+      const float pairs = s * (float)Hkv, most = ceilf(pairs * 0.125f);
+      const float wgs = most * (float)mtiles;
+      const float one = (float)min(L, rmax) * (1.f / 64.f) + rc.fixed;
+      const float steps = keys * (float)mtiles * (1.f / 64.f) * (most / fmaxf(pairs, 1.f));
+      const float time =
+          wgs <= kXcdCus ? one
+                         : fminf(ceilf(wgs / kXcdCus) * one,
+                                 (steps + wgs * rc.fixed) / kXcdCus + rc.tail * one);
+      const float cost = time + rc.part * ceilf((float)rmax * inv - 1e-4f);
       // the least cost: positive floats order like their bits
       const int key = 0x7FFFFFFF - (int)__float_as_uint(cost);
       L = __builtin_amdgcn_readlane(L, __ffsll((long long)__ballot(key == wave_max_nonneg(key))) - 1);
@@ -273,7 +283,7 @@ __global__ __launch_bounds__(256) void attn_bf16_w4_kernel(
     const int32_t* __restrict__ ctxp, const int32_t* __restrict__ parentp,
     const int32_t* __restrict__ nnp, int N, int Hq, int Hkv, int max_ctx, float scale_log2,
     int split_len, int splits, int mtiles, int pairs, int mrows_pad, void* __restrict__ wsO,
-    float2* __restrict__ wsML, int batch, int target_pairs, RaggedCost rc, int lcap,
+    float2* __restrict__ wsML, int batch, int target_pairs, int lcap,
     int2* __restrict__ tab) {
   // the body uses the buffer-resource type, which exists only in the device pass; the
   // host pass needs no more than the signature to emit the launch stub
@@ -317,7 +327,7 @@ __global__ __launch_bounds__(256) void attn_bf16_w4_kernel(
     g = bg - b * Hkv;
   } else {
     const RaggedPick rp = ragged_pick(ctxp, nnp, batch, N, max_ctx, Hkv, mtiles, target_pairs,
-                                      rc, lcap, split_len, pair, tab,
+                                      ragged_cost(HD), lcap, split_len, pair, tab,
                                       pair == 0 && mt == 0 && (threadIdx.x >> 6) == 0);
     if (!rp.found) return;   // past the batch's pairs (nothing issued yet)
     b = __builtin_amdgcn_readfirstlane(rp.b);
@@ -571,11 +581,12 @@ __global__ __launch_bounds__(256) void attn_bf16_w4_kernel(
   const float lsum = l_run + other_half(l_run);
   const float inv = lsum > 0.f ? 1.f / lsum : 0.f;
 
-  // ---- write this split's partial: O / sum (fp32 for the ragged list, else bf16),
-  // reference max and sum
+  // ---- write this split's partial: O / sum (fp32 for the ragged list's cut requests, else
+  // bf16), reference max and sum
   const size_t obase = (size_t)pair * mrows_pad;
   const int qr = row0 + rg * 32 + l32;
-  const size_t orow = (obase + qr) * HD;
+  const bool wide = tab != nullptr && R > split_len;
+  unsigned char* const orow = (unsigned char*)wsO + (obase + qr) * (HD * (tab != nullptr ? 4 : 2));
 #pragma unroll
   for (int db = 0; db < NDB; ++db)
 #pragma unroll
@@ -584,19 +595,13 @@ __global__ __launch_bounds__(256) void attn_bf16_w4_kernel(
       float x[4];
 #pragma unroll
       for (int t = 0; t < 4; ++t) x[t] = o[db][4 * r4 + t] * inv;
-      if (tab != nullptr) *(float4*)((float*)wsO + orow + d) = make_float4(x[0], x[1], x[2], x[3]);
-      else *(uint2*)((uint16_t*)wsO + orow + d) = pack_bf16x4(x[0], x[1], x[2], x[3]);
+      if (wide) *(float4*)(orow + 4 * d) = make_float4(x[0], x[1], x[2], x[3]);
+      else *(uint2*)(orow + 2 * d) = pack_bf16x4(x[0], x[1], x[2], x[3]);
     }
   if (hl == 0) wsML[obase + qr] = make_float2(m_ref, lsum);
 #endif
 }
 
-// Eight waves per workgroup (two per SIMD), in two key groups of four: group g works on
-// the 32-key stages g, g + 2, g + 4, ... of the split, each wave on 32 query rows, and
-// the groups merge their results through LDS at the end.  K and V cycle through rings of
-// eight 32-key slots.  Their 16-byte chunks are XOR-permuted by kswz16, which measures
-// 256 B/clk per CU for the K reads and 201 for the transposing V reads (three-bit kswz: 128
-// for both).
 // Division of small non-negative ints by the launch's tile, split, head and group
 // counts: floor(n / d) = high half of n * ceil(2^32 / d), exact for n < 2^32 / d (the
 // rounding term of the multiplier adds less than n / 2^32 < 1/d to n / d)
@@ -672,14 +677,20 @@ struct GroupTag {
 // buffer-resource type, which exists only in the device pass; the host pass needs no more
 // than the kernels' signatures to emit their launch stubs.
 #if defined(__HIP_DEVICE_COMPILE__)
-template <bool PAGED>
+// Eight waves per workgroup (two per SIMD), in two key groups of four: group g works on
+// the 32-key stages g, g + 2, g + 4, ... of the split, each wave on 32 query rows, and
+// the groups merge their results through LDS at the end.  K and V cycle through rings of
+// eight 32-key slots.  Their 16-byte chunks are XOR-permuted by kswz16, which measures
+// 256 B/clk per CU for the K reads and 201 for the transposing V reads (three-bit kswz: 128
+// for both).
+template <bool PAGED, bool MULTI>
 __device__ __attribute__((always_inline)) inline void attn_bf16_body(
     const uint16_t* __restrict__ Q, const uint16_t* __restrict__ Kc,
     const uint16_t* __restrict__ Vc, const int64_t* __restrict__ offp,
     const int32_t* __restrict__ ctxp, const int32_t* __restrict__ parentp,
     const int32_t* __restrict__ nnp, int N, int Hq, int Hkv, int max_ctx, float scale_log2,
     int split_len, int splits, int mtiles, int pairs, int mrows_pad, void* __restrict__ wsO,
-    float2* __restrict__ wsML, DivMagic dm, int batch, int target_pairs, RaggedCost rc, int lcap,
+    float2* __restrict__ wsML, DivMagic dm, int batch, int target_pairs, int lcap,
     int2* __restrict__ tab, const PagedKV& pk) {
   constexpr int HD = 128;
   constexpr int NT = 512;
@@ -716,17 +727,18 @@ __device__ __attribute__((always_inline)) inline void attn_bf16_body(
   const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
   const int sq = dm.div(slot, mtiles, dm.mt);
   const int mt = slot - sq * mtiles;
-  const int pair = tab == nullptr ? xcd * ((pairs + 7) >> 3) + sq : sq * 8 + xcd;
+  const bool list = MULTI && tab != nullptr;
+  const int pair = !list ? xcd * ((pairs + 7) >> 3) + sq : sq * 8 + xcd;
   if (pair >= pairs) return;
   int b, g, split;
-  if (tab == nullptr) {
+  if (!list) {
     const int bg = dm.div(pair, splits, dm.sp);
     split = pair - bg * splits;
     b = dm.div(bg, Hkv, dm.hk);
     g = bg - b * Hkv;
   } else {
     const RaggedPick rp = ragged_pick(ctxp, nnp, batch, N, max_ctx, Hkv, mtiles, target_pairs,
-                                      rc, lcap, split_len, pair, tab,
+                                      ragged_cost(HD), lcap, split_len, pair, tab,
                                       pair == 0 && mt == 0 && (threadIdx.x >> 6) == 0);
     if (!rp.found) return;   // past the batch's pairs (nothing issued yet)
     b = __builtin_amdgcn_readfirstlane(rp.b);
@@ -1195,9 +1207,10 @@ __device__ __attribute__((always_inline)) inline void attn_bf16_body(
   const float inv = Ls > 0.f ? 1.f / Ls : 0.f;
 
   // ---- write this split's partial: O / sum for this group's 64 head dims of the wave's 32
-  // rows (fp32 for the ragged list, else bf16), max and sum.  The tile goes through LDS (this
-  // wave's V slot, free now), 128 bytes of every row at a time: both head blocks in bf16, one
-  // in fp32.  So each store instruction writes whole 128-byte row segments.  The stores are
+  // rows (of several requests in fp32, but for the ragged list's uncut ones, else in bf16), max
+  // and sum.  The tile goes
+  // through LDS (this wave's V slot, free now), 128 bytes of every row at a time: both head
+  // blocks in bf16, one in fp32.  So each store instruction writes whole 128-byte row segments.  The stores are
   // non-temporal: only the combine, a later launch, reads the partials, and streaming them
   // out of the L2 leaves less to write back when the kernel ends (measured: the kernel took
   // 0.5 us less at the Qwen3-8B shape).
@@ -1205,13 +1218,15 @@ __device__ __attribute__((always_inline)) inline void attn_bf16_body(
   unsigned char* const stage = s_v + wave * TILEB;
   const size_t obase = (size_t)pair * mrows_pad;
   const int qbase = row0 + rg * 32;
+  const bool wide = MULTI && (!list || R > split_len);
   auto wave_sync = []() __attribute__((always_inline)) {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   };
-  // the staged 128 bytes of every row to byte `at` of the rows' partials of `rowb` bytes
-  auto flush = [&](int rowb, int at) __attribute__((always_inline)) {
+  // the staged 128 bytes of every row to byte `at` of the rows' partials
+  constexpr size_t rowb = HD * (MULTI ? 4 : 2);
+  auto flush = [&](int at) __attribute__((always_inline)) {
     wave_sync();
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -1234,14 +1249,14 @@ __device__ __attribute__((always_inline)) inline void attn_bf16_body(
 #pragma unroll
       for (int t = 0; t < 4; ++t) x[t] = (own[4 * r4 + t] * a0 + tv[t] * a1) * inv;
       const int d = 8 * r4 + 4 * hl;
-      if (tab != nullptr)
+      if (wide)
         *(float4*)(stage + l32 * TROW + 4 * d) = make_float4(x[0], x[1], x[2], x[3]);
       else
         *(uint2*)(stage + l32 * TROW + 2 * (j * 32 + d)) = pack_bf16x4(x[0], x[1], x[2], x[3]);
     }
-    if (tab != nullptr) flush(HD * 4, kg * 256 + j * 128);
+    if (wide) flush(kg * 256 + j * 128);
   }
-  if (tab == nullptr) flush(HD * 2, kg * 128);
+  if (!wide) flush(kg * 128);
   const int qr = qbase + l32;
   if (kg == 0 && hl == 0) {
     f32x2 ml2;
@@ -1252,35 +1267,39 @@ __device__ __attribute__((always_inline)) inline void attn_bf16_body(
 }
 #endif
 
-// Contiguous cache: the kernel keeps exactly the arguments it had before the paged mode
-// existed (a longer argument block measured 0.3 us slower per launch, same code).
+// Contiguous cache, without the page table's arguments (a longer argument block measured 0.3
+// us slower per launch, same code).  MULTI: several requests; one request takes a kernel
+// without the list's choice and the fp32 partials (15.8 us at the Qwen3-8B shape in a kernel
+// trace, 16.2 with them in it).
+template <bool MULTI>
 __global__ __launch_bounds__(512) void attn_bf16_kernel(
     const uint16_t* __restrict__ Q, const uint16_t* __restrict__ Kc,
     const uint16_t* __restrict__ Vc, const int64_t* __restrict__ offp,
     const int32_t* __restrict__ ctxp, const int32_t* __restrict__ parentp,
     const int32_t* __restrict__ nnp, int N, int Hq, int Hkv, int max_ctx, float scale_log2,
     int split_len, int splits, int mtiles, int pairs, int mrows_pad, void* __restrict__ wsO,
-    float2* __restrict__ wsML, DivMagic dm, int batch, int target_pairs, RaggedCost rc, int lcap,
+    float2* __restrict__ wsML, DivMagic dm, int batch, int target_pairs, int lcap,
     int2* __restrict__ tab) {
 #if defined(__HIP_DEVICE_COMPILE__)
-  attn_bf16_body<false>(Q, Kc, Vc, offp, ctxp, parentp, nnp, N, Hq, Hkv, max_ctx, scale_log2, split_len,
-                       splits, mtiles, pairs, mrows_pad, wsO, wsML, dm, batch, target_pairs, rc, lcap,
+  attn_bf16_body<false, MULTI>(Q, Kc, Vc, offp, ctxp, parentp, nnp, N, Hq, Hkv, max_ctx, scale_log2, split_len,
+                       splits, mtiles, pairs, mrows_pad, wsO, wsML, dm, batch, target_pairs, lcap,
                        tab, PagedKV{nullptr, 0, 1, 5});
 #endif
 }
 
 // Paged cache (C20 of the readings: tree_verify_attn_paged)
+template <bool MULTI>
 __global__ __launch_bounds__(512) void attn_bf16_paged_kernel(
     const uint16_t* __restrict__ Q, const uint16_t* __restrict__ Kc,
     const uint16_t* __restrict__ Vc, const int64_t* __restrict__ offp,
     const int32_t* __restrict__ ctxp, const int32_t* __restrict__ parentp,
     const int32_t* __restrict__ nnp, int N, int Hq, int Hkv, int max_ctx, float scale_log2,
     int split_len, int splits, int mtiles, int pairs, int mrows_pad, void* __restrict__ wsO,
-    float2* __restrict__ wsML, DivMagic dm, int batch, int target_pairs, RaggedCost rc, int lcap,
+    float2* __restrict__ wsML, DivMagic dm, int batch, int target_pairs, int lcap,
     int2* __restrict__ tab, PagedKV pk) {
 #if defined(__HIP_DEVICE_COMPILE__)
-  attn_bf16_body<true>(Q, Kc, Vc, offp, ctxp, parentp, nnp, N, Hq, Hkv, max_ctx, scale_log2, split_len,
-                       splits, mtiles, pairs, mrows_pad, wsO, wsML, dm, batch, target_pairs, rc, lcap,
+  attn_bf16_body<true, MULTI>(Q, Kc, Vc, offp, ctxp, parentp, nnp, N, Hq, Hkv, max_ctx, scale_log2, split_len,
+                       splits, mtiles, pairs, mrows_pad, wsO, wsML, dm, batch, target_pairs, lcap,
                        tab, pk);
 #endif
 }
@@ -1292,7 +1311,7 @@ __global__ __launch_bounds__(512) void attn_bf16_paged_kernel(
 // spread over 256 workgroups, one per CU, and each CU pulls half as many partials (the
 // combine took 4.7 us against 5.0 us with 256 threads).
 constexpr int kCombineThreads = 128;
-template <int HD, int CH, bool RAGGED>
+template <int HD, int CH, bool WIDE>
 __global__ __launch_bounds__(kCombineThreads) void attn_combine_kernel(
     const void* __restrict__ wsO, const float2* __restrict__ wsML,
     const int32_t* __restrict__ ctxp, const int32_t* __restrict__ nnp, int N, int Hq, int Hkv,
@@ -1314,7 +1333,7 @@ __global__ __launch_bounds__(kCombineThreads) void attn_combine_kernel(
   // table, written by the attention kernel, or the host's fixed split count)
   size_t base;
   int cap;
-  if constexpr (RAGGED) {
+  if (WIDE && tab != nullptr) {
     const int2 t = tab[b];
     base = (size_t)t.x + (size_t)g * t.y;
     cap = t.y;
@@ -1323,13 +1342,13 @@ __global__ __launch_bounds__(kCombineThreads) void attn_combine_kernel(
     base = (size_t)(b * Hkv + g) * splits;
     cap = splits;
   }
-  // each split holds O_s / l_s (fp32 for the ragged list, else bf16) and (m_s, l_s) with m_s
-  // in base 2:
+  // each split holds O_s / l_s (bf16; with WIDE fp32, but for the ragged list's uncut
+  // requests) and (m_s, l_s) with m_s in base 2:
   // O = sum_s 2^(m_s - M) l_s (O_s / l_s) / sum_s 2^(m_s - M) l_s.  The loads of the first
   // CH splits go out before the request's sizes are known (their addresses do not depend on
   // them; splits past the request's keys are masked once the sizes have arrived), then
   // groups of up to CH splits are merged with a running maximum.
-  constexpr int NV = RAGGED ? 2 : 1;   // 16-byte loads of the 8 values
+  constexpr int NV = WIDE ? 2 : 1;   // 16-byte loads of the 8 values
   float2 ml[CH];
   uint4 ov[CH][NV];
   auto load_group = [&](int s0) __attribute__((always_inline)) {
@@ -1342,11 +1361,32 @@ __global__ __launch_bounds__(kCombineThreads) void attn_combine_kernel(
         ov[t][v] = *(const uint4*)((const unsigned char*)wsO + (r * HD + d) * (2 * NV) + 16 * v);
     }
   };
-  if (cap > 0) load_group(0);
+  const bool uncut = WIDE && tab != nullptr && cap == 1;   // uniform
+  if (uncut) {
+    const size_t r = base * mrows_pad + qr;
+    ml[0] = wsML[r];
+    ov[0][0] = *(const uint4*)((const unsigned char*)wsO + r * (HD * 4) + 2 * d);
+  } else if (cap > 0) {
+    load_group(0);
+  }
   int ctx_raw, n_raw;
   load_two_scalars(ctxp + b, nnp + b, ctx_raw, n_raw);
   const int n = min(max(n_raw, 0), N);
   if (i >= n) return;
+  uint16_t* const out = O + (((size_t)b * N + i) * Hq + hq) * HD + d;
+  if (uncut) {   // the same sums with one term
+    const float w = ml[0].x == -INFINITY ? 0.f : ml[0].y, inv = 1.f / w;
+    const uint32_t wd[4] = {ov[0][0].x, ov[0][0].y, ov[0][0].z, ov[0][0].w};
+    float x[8];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      x[2 * k] = w * __uint_as_float(wd[k] << 16) * inv;
+      x[2 * k + 1] = w * __uint_as_float(wd[k] & 0xFFFF0000u) * inv;
+    }
+    const uint2 lo = pack_bf16x4(x[0], x[1], x[2], x[3]), hi = pack_bf16x4(x[4], x[5], x[6], x[7]);
+    *(uint4*)out = make_uint4(lo.x, lo.y, hi.x, hi.y);
+    return;
+  }
   const int ctx = min(max(ctx_raw, 0), max_ctx);
   const int R = ctx + n;
   const int nspl = min((R + split_len - 1) / split_len, cap);
@@ -1381,7 +1421,7 @@ __global__ __launch_bounds__(kCombineThreads) void attn_combine_kernel(
         const uint32_t wd[4] = {ov[t][v].x, ov[t][v].y, ov[t][v].z, ov[t][v].w};
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-          if constexpr (RAGGED) {
+          if constexpr (WIDE) {
             acc[4 * v + k] += w * __uint_as_float(wd[k]);
           } else {
             acc[2 * k] += w * __uint_as_float(wd[k] << 16);
@@ -1395,7 +1435,7 @@ __global__ __launch_bounds__(kCombineThreads) void attn_combine_kernel(
   const float inv = 1.f / L;
   const uint2 lo = pack_bf16x4(acc[0] * inv, acc[1] * inv, acc[2] * inv, acc[3] * inv);
   const uint2 hi = pack_bf16x4(acc[4] * inv, acc[5] * inv, acc[6] * inv, acc[7] * inv);
-  *(uint4*)(O + (((size_t)b * N + i) * Hq + hq) * HD + d) = make_uint4(lo.x, lo.y, hi.x, hi.y);
+  *(uint4*)out = make_uint4(lo.x, lo.y, hi.x, hi.y);
 }
 
 }  // namespace
@@ -1405,8 +1445,6 @@ AttnPlan plan_attn(int batch, int budget, int Hq, int Hkv, int head_dim, int max
   AttnPlan p;
   const int G = Hq / Hkv;
   const int mrows = budget * G;
-  p.qb = 1;
-  p.wk = 1;
   p.mtile = 4 * 32;
   p.mtiles = (mrows + p.mtile - 1) / p.mtile;
   p.ragged = 0;
@@ -1423,16 +1461,14 @@ AttnPlan plan_attn(int batch, int budget, int Hq, int Hkv, int head_dim, int max
   const int keys = max_ctx + budget;
   const int step = kKT;
   const long long base = (long long)batch * Hkv * p.mtiles;
-  p.resident = 256;
-  p.fixed = 8;
   int splits = 1;
   long long best = -1;
   for (int s = 1; s <= 64; ++s) {
     int l = (keys + s - 1) / s;
     l = ((l + step - 1) / step) * step;
     if (l < 2 * step) l = 2 * step;
-    const long long rounds = (base * s + p.resident - 1) / p.resident;
-    const long long cost = rounds * (l / step + p.fixed);
+    const long long rounds = (base * s + 255) / 256;
+    const long long cost = rounds * (l / step + 8);
     if (best < 0 || cost < best) {
       best = cost;
       splits = s;
@@ -1447,33 +1483,46 @@ AttnPlan plan_attn(int batch, int budget, int Hq, int Hkv, int head_dim, int max
   if (batch > 1) {
     // Several requests: their lengths are known only on the device, where the kernel picks
     // the split length (ragged_pick): this plan's for lengths close to each other, else the
-    // best by its estimate, up to about four workgroups per CU.  Measured against a fixed
-    // three workgroups per CU (us, 32/8 heads, head_dim 128, with the combine): 4 requests of
-    // 700-6K keys over pages 64.1 -> 44.0, 3 of 700-20K 47.7 -> 35.7, 8 of 300-9K 91 -> 75,
-    // 16 of 512-16K 235 -> 209; head_dim 64 against every request split for max_ctx: 16 of
-    // 512-16K 210 -> 133, 4 of 2-8K 33.8 -> 31.2.  (Two head_dim 64 workgroups fit a CU, but
-    // the softmax bounds both: counting on 512 at a time took 8 requests of 300-3K from 17.6
-    // to 21.3 us.)
-    const int target = (1024 + p.mtiles - 1) / p.mtiles;
-    const long long worst = ((long long)batch * (max_ctx + budget) * Hkv + target - 1) / target;
+    // best by its estimate.  Figures: us of attention and combine, 32/8 heads of 128 unless
+    // named, every request cut for max_ctx -> the list: 16 requests of 512-16K keys 276 ->
+    // 219, 4 of 700-6K over pages 59 -> 43, 3 of 700-20K 58 -> 34, 8 of 300-9K over pages 75
+    // -> 43; head_dim 64: 16 of 512-16K 185 -> 133, 4 of 2-8K 31.3 -> 28.9.
+    // * The list has room for one workgroup per CU (head_dim 64, where two fit: two) where
+    //   the most work there can be is small, for four beyond: a workgroup past the batch's
+    //   pairs still reads the lengths and makes the choice, ~1 us, and at head_dim 128 it
+    //   waits for a CU.  Against room for four everywhere: 3 requests of 700-20K keys 39.8 ->
+    //   34.3, 3 of 1.1-3.1K (16/2 heads, 95 nodes) 26.3 -> 23.6.
+    // * Less work takes no list: the choice, the table in the combine and the idle workgroups
+    //   cost 1-3 us.  List -> none, with the steps of the most work: 4 of 1.6-3.7K (16/2
+    //   heads, 41 nodes, 1.4K steps) 20.2 -> 17.9, 7 of 285-455 (30 nodes, 0.4K) 17.9 ->
+    //   16.6, but 3 of 1.1-3.1K (above, 1.8K) 23.6 -> 24.7; head_dim 64: 2 of 3-9K (63 nodes,
+    //   4.6K) 24.2 -> 22.3, 12 of 164-315 (16/8 heads, 180 nodes, 2.2K) 26.2 -> 25.3, but 14
+    //   of 280-1.2K (40/8, 74 nodes, 6.5K) 30.9 -> 34.7.
+    const long long steps = base * keys / kKT;
+    const int wgs = head_dim == 128 ? (steps <= 32768 ? 256 : 1024) : steps <= 32768 ? 512 : 1024;
+    int target = (wgs + p.mtiles - 1) / p.mtiles;
+    auto worst = [&] { return ((long long)batch * keys * Hkv + target - 1) / target; };
+    if (worst() > p.lcap) target = (1024 + p.mtiles - 1) / p.mtiles;
     const long long pm = std::max((long long)target + (long long)batch * Hkv,
                                   (long long)batch * Hkv * p.splits);
-    if (worst <= p.lcap && pm < (1ll << 24)) {
+    if (worst() <= p.lcap && pm < (1ll << 24) && steps >= (head_dim == 128 ? 1536 : 6144)) {
       p.ragged = 1;
       p.target_pairs = target;
       p.pairs_max = (int)pm;
     }
   }
+  p.wide = p.ragged || (batch > 1 && head_dim == 128);
   return p;
 }
 
 // split partials [slot][mtiles * mtile][head_dim], then their (max, sum) pairs, then (ragged
-// list) the per-request table of the combine.  The ragged list's partials are fp32: its split
-// lengths follow the batch, and a partial rounded to bf16 would give a request cut in two a
-// quarter more error than the same request uncut (2.9e-3 against 2.3e-3 of the result).  The
-// wider partials cost 9 us of 207 at 16 requests of 512-16K keys (32/8 heads of 128), 0.5 of
-// 28.8 at 4 of 2-8K with head_dim 64, 5 of 548 at 4 x 32K keys.
-static size_t attn_part_bytes(const AttnPlan& pl) { return pl.ragged ? 4 : 2; }
+// list) the per-request table of the combine.  Partials are bf16, but fp32 (pl.wide) where the
+// batch's lengths decide how a request is cut: a partial rounded to bf16 gives a request cut
+// in two a quarter more error than the same request uncut (2.9e-3 against 2.3e-3 of the
+// result).  A request that the ragged list leaves uncut is rounded once in any case and keeps
+// the shorter ones.  fp32 costs 8 us of 213 at 16 requests of 512-16K keys (32/8 heads of
+// 128), 0.6 of 28.7 at 4 of 2-8K with head_dim 64.
+static size_t attn_part_bytes(const AttnPlan& pl) { return pl.wide ? 4 : 2; }
 static size_t attn_rows(const AttnPlan& pl, int batch, int Hkv) {
   const size_t slots = pl.ragged ? (size_t)pl.pairs_max : (size_t)batch * Hkv * pl.splits;
   return slots * (size_t)pl.mtiles * pl.mtile;
@@ -1509,7 +1558,6 @@ static hipError_t launch_attn_bf16_impl(const void* Q, const void* K, const void
   dim3 grid((unsigned)(8 * pl.mtiles * ((pairs + 7) / 8)));
   dim3 block(256u);
   const float sl2 = scale * kLog2e;
-  const RaggedCost rc{pl.resident, pl.fixed};
   const uint16_t *q = (const uint16_t*)Q, *k = (const uint16_t*)K, *v = (const uint16_t*)V;
   // with events, the launch records the kernel's own start and end (hipExtLaunchKernel)
   if (head_dim == 128) {
@@ -1517,47 +1565,48 @@ static hipError_t launch_attn_bf16_impl(const void* Q, const void* K, const void
     const DivMagic dm{DivMagic::make(pl.mtiles), DivMagic::make(pl.splits), DivMagic::make(Hkv),
                       DivMagic::make(Hq / Hkv)};
     if constexpr (PAGED) {
+      const auto kernel = batch > 1 ? attn_bf16_paged_kernel<true> : attn_bf16_paged_kernel<false>;
       if (ev_begin || ev_end)
-        hipExtLaunchKernelGGL(attn_bf16_paged_kernel, grid, block8, 0, s, ev_begin, ev_end, 0,
+        hipExtLaunchKernelGGL(kernel, grid, block8, 0, s, ev_begin, ev_end, 0,
                               q, k, v, off, ctx, parent, n, budget, Hq, Hkv, max_ctx, sl2,
                               pl.split_len, pl.splits, pl.mtiles, pairs, mrows_pad, wsO, wsML,
-                              dm, batch, pl.target_pairs, rc, pl.lcap, tab, pk);
+                              dm, batch, pl.target_pairs, pl.lcap, tab, pk);
       else
-        attn_bf16_paged_kernel<<<grid, block8, 0, s>>>(
+        kernel<<<grid, block8, 0, s>>>(
             q, k, v, off, ctx, parent, n, budget, Hq, Hkv, max_ctx, sl2, pl.split_len, pl.splits,
-            pl.mtiles, pairs, mrows_pad, wsO, wsML, dm, batch, pl.target_pairs, rc, pl.lcap, tab, pk);
+            pl.mtiles, pairs, mrows_pad, wsO, wsML, dm, batch, pl.target_pairs, pl.lcap, tab, pk);
     } else {
+      const auto kernel = batch > 1 ? attn_bf16_kernel<true> : attn_bf16_kernel<false>;
       if (ev_begin || ev_end)
-        hipExtLaunchKernelGGL(attn_bf16_kernel, grid, block8, 0, s, ev_begin, ev_end, 0, q, k,
+        hipExtLaunchKernelGGL(kernel, grid, block8, 0, s, ev_begin, ev_end, 0, q, k,
                               v, off, ctx, parent, n, budget, Hq, Hkv, max_ctx, sl2,
                               pl.split_len, pl.splits, pl.mtiles, pairs, mrows_pad, wsO, wsML,
-                              dm, batch, pl.target_pairs, rc, pl.lcap, tab);
+                              dm, batch, pl.target_pairs, pl.lcap, tab);
       else
-        attn_bf16_kernel<<<grid, block8, 0, s>>>(q, k, v, off, ctx, parent, n, budget, Hq, Hkv,
-                                                 max_ctx, sl2, pl.split_len, pl.splits,
-                                                 pl.mtiles, pairs, mrows_pad, wsO, wsML, dm,
-                                                 batch, pl.target_pairs, rc, pl.lcap, tab);
+        kernel<<<grid, block8, 0, s>>>(q, k, v, off, ctx, parent, n, budget, Hq, Hkv, max_ctx, sl2,
+                                       pl.split_len, pl.splits, pl.mtiles, pairs, mrows_pad, wsO,
+                                       wsML, dm, batch, pl.target_pairs, pl.lcap, tab);
     }
   } else if constexpr (!PAGED) {
     if (ev_begin || ev_end)
       hipExtLaunchKernelGGL(attn_bf16_w4_kernel<64>, grid, block, 0, s, ev_begin, ev_end, 0, q,
                             k, v, off, ctx, parent, n, budget, Hq, Hkv, max_ctx, sl2,
                             pl.split_len, pl.splits, pl.mtiles, pairs, mrows_pad, wsO, wsML, batch,
-                            pl.target_pairs, rc, pl.lcap, tab);
+                            pl.target_pairs, pl.lcap, tab);
     else
       attn_bf16_w4_kernel<64><<<grid, block, 0, s>>>(q, k, v, off, ctx, parent, n, budget, Hq,
                                                      Hkv, max_ctx, sl2, pl.split_len,
                                                      pl.splits, pl.mtiles, pairs, mrows_pad,
                                                      wsO, wsML, batch, pl.target_pairs,
-                                                     rc, pl.lcap, tab);
+                                                     pl.lcap, tab);
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const int rows_req = budget * Hq;   // output rows of one request
   const DivMagic cm{0u, 0u, DivMagic::make(Hq), DivMagic::make(Hq / Hkv)};
-  // splits per group: the one-request plan's split count (rounded up to 4, 8 or 16), 4
+  // splits per group: the plan's split count, rounded up to 4, 8 or 16 (fp32: 8 at most), 4
   // for the ragged list
-  const int ch = pl.splits <= 4 ? 4 : pl.splits <= 8 ? 8 : 16;
+  const int ch = pl.splits <= 4 || tab != nullptr ? 4 : pl.splits <= 8 || pl.wide ? 8 : 16;
 #define TAPS_COMBINE(HDC, CHC, RG)                                                           \
   attn_combine_kernel<HDC, CHC, RG>                                                          \
       <<<dim3((unsigned)((rows_req + kCombineThreads / (HDC / 8) - 1) /                      \
@@ -1566,17 +1615,18 @@ static hipError_t launch_attn_bf16_impl(const void* Q, const void* K, const void
          dim3(kCombineThreads), 0, s>>>(wsO, wsML, ctx, n, budget, Hq, Hkv, max_ctx,          \
                                         pl.split_len, pl.splits, mrows_pad, cm, (uint16_t*)O, \
                                         tab, batch)
-  if (head_dim == 128) {
-    if (tab != nullptr) TAPS_COMBINE(128, 4, true);
-    else if (ch == 4) TAPS_COMBINE(128, 4, false);
-    else if (ch == 8) TAPS_COMBINE(128, 8, false);
-    else TAPS_COMBINE(128, 16, false);
-  } else {
-    if (tab != nullptr) TAPS_COMBINE(64, 4, true);
-    else if (ch == 4) TAPS_COMBINE(64, 4, false);
-    else if (ch == 8) TAPS_COMBINE(64, 8, false);
-    else TAPS_COMBINE(64, 16, false);
-  }
+#define TAPS_COMBINE_HD(HDC)                           \
+  do {                                                 \
+    if (pl.wide) {                                     \
+      if (ch == 4) TAPS_COMBINE(HDC, 4, true);         \
+      else TAPS_COMBINE(HDC, 8, true);                 \
+    } else if (ch == 4) TAPS_COMBINE(HDC, 4, false);   \
+    else if (ch == 8) TAPS_COMBINE(HDC, 8, false);     \
+    else TAPS_COMBINE(HDC, 16, false);                 \
+  } while (0)
+  if (head_dim == 128) TAPS_COMBINE_HD(128);
+  else TAPS_COMBINE_HD(64);
+#undef TAPS_COMBINE_HD
 #undef TAPS_COMBINE
   return hipGetLastError();
 }

@@ -57,19 +57,16 @@ hipError_t launch_marginal_z(const void* marg, int dtype, int rows, int vocab, i
                              int64_t* spart, hipStream_t s);
 
 struct AttnPlan {
-  int qb;          // 32-row query blocks per wave (1 or 2)
-  int wk;          // key groups per workgroup (1 or 2): 256 * wk threads
   int mtile;       // query rows per workgroup (4 waves)
   int mtiles;      // workgroups along the budget*G query rows of one KV head
   int split_len;   // keys per split (multiple of 64)
   int splits;      // splits along max_ctx + budget keys
+  int wide;        // split partials in fp32 (else bf16)
   // Ragged work list (several requests): the kernel sizes the splits from the requests'
-  // actual keys for up to target_pairs (request, KV head, split) pairs, by an estimate with
-  // `resident` workgroups at a time and `fixed` 64-key steps' worth of work outside the key
-  // loop in each; at most pairs_max; split lengths at most lcap keys
+  // actual keys for about target_pairs (request, KV head, split) pairs at most, by an estimate
+  // of the batch's time; at most pairs_max; split lengths at most lcap keys
   int ragged;
   int target_pairs;
-  int resident, fixed;
   int pairs_max;
   int lcap;
 };

@@ -22,29 +22,37 @@ def taps():
     return taps
 
 
-def _branch(R, N, Hq, Hkv):
-    """The branch of the kernel's choice for requests of R keys: the host's length ("host"),
-    128-key splits that all fit the 256 CUs ("short"), more requests than a wave has lanes
-    ("many"), or the cheapest of 64 lengths ("search")."""
-    units = Hkv * -(-N * (Hq // Hkv) // 128)
+def _branch(R, max_ctx, N, Hq, Hkv, hd):
+    """The branch of the choice for requests of R keys: little work, every request cut for
+    max_ctx without a list ("plain"); the list with the host's length ("host"), for more requests
+    than a wave has lanes ("many") or with the cheapest of 64 lengths ("search")."""
+    steps = len(R) * Hkv * -(-N * (Hq // Hkv) // 128) * (max_ctx + N) // 64
+    if steps < (1536 if hd == 128 else 6144):
+        return "plain"
     if 4 * max(R) * len(R) <= 5 * sum(R):
         return "host"
-    if len(R) > 64:
-        return "many"
-    return "short" if sum(-(-r // 128) for r in R) * units <= 256 else "search"
+    return "many" if len(R) > 64 else "search"
 
 
-@pytest.mark.parametrize("hd", [64, 128])
-@pytest.mark.parametrize("ctx,N,Hq,Hkv,branch", [
-    ([3000, 5], 9, 4, 2, "short"), ([500, 510, 505], 40, 8, 2, "host"), ([0, 0], 1, 2, 1, "host"),
-    ([700, 1400, 2100, 64, 0], 33, 8, 2, "short"),
-    ([(37 * i * i) % 900 for i in range(70)], 5, 4, 1, "many"),
-    ([6000, 40, 2500, 0], 64, 16, 4, "search"),
-    ([(97 * i * i) % 3000 for i in range(64)], 5, 4, 1, "search"),
-    ([7100, 900], 32, 8, 4, "short"),      # 64 splits of 4 units: just the chip
-    ([7169, 900], 32, 8, 4, "search"),     # one split more
-    ([2000, 1170], 16, 8, 8, "short"),     # just past the 5/4 of the mean
-    ([2000, 1200], 16, 8, 8, "host")])     # just within it
+SQ70 = [(37 * i * i) % 900 for i in range(70)]
+SQ64 = [(97 * i * i) % 3000 for i in range(64)]
+
+
+@pytest.mark.parametrize("hd,ctx,N,Hq,Hkv,branch", [
+    (hd, *c, "plain") for hd in (64, 128) for c in [
+        ([3000, 5], 9, 4, 2), ([500, 510, 505], 40, 8, 2), ([0, 0], 1, 2, 1),
+        ([700, 1400, 2100, 64, 0], 33, 8, 2), (SQ70, 5, 4, 1)]] + [
+    (128, [6000, 40, 2500, 0], 64, 16, 4, "search"), (128, SQ64, 5, 4, 1, "search"),
+    (128, SQ70, 5, 4, 2, "many"),
+    (128, [6200, 3710], 16, 8, 8, "search"),     # just past the 5/4 of the mean
+    (128, [6200, 3720], 16, 8, 8, "host"),       # just within it
+    (128, [6128, 10], 16, 8, 8, "search"),       # 1536 steps of 64 keys
+    (128, [6127, 10], 16, 8, 8, "plain"),        # one key fewer
+    (64, [6200, 40, 2500, 0], 64, 32, 8, "search"), (64, SQ70, 5, 8, 8, "many"),
+    (64, SQ64, 5, 8, 4, "search"), (64, [2100, 2000, 2050, 1800, 1700, 2010], 128, 32, 8, "host"),
+    (64, [6080, 100], 64, 64, 16, "search"),     # 6144 steps of 64 keys
+    (64, [6079, 100], 64, 64, 16, "plain"),      # one key fewer
+])
 def test_ragged_pick(taps, hd, ctx, N, Hq, Hkv, branch):
     rng = np.random.default_rng(len(ctx) + hd)
     B, ctx = len(ctx), np.array(ctx, dtype=np.int32)
@@ -56,7 +64,8 @@ def test_ragged_pick(taps, hd, ctx, N, Hq, Hkv, branch):
     parents = [np.array([-1] + [int(rng.integers(max(0, i - 3), i)) for i in range(1, N)],
                         dtype=np.int32) for _ in range(B)]
     n = [N if b % 3 else max(1, N - 2) for b in range(B)]
-    assert _branch([int(c) + k for c, k in zip(ctx, n)], N, Hq, Hkv) == branch
+    R = [int(c) + k for c, k in zip(ctx, n)]
+    assert _branch(R, int(max(ctx.max(), 1)), N, Hq, Hkv, hd) == branch
     att = taps.TreeAttention(B, N, Hq, Hkv, hd, int(max(ctx.max(), 1)), dtype=BF16)
     att.ws.fill_(0xFF)            # NaN bits in every unwritten partial slot
     O = att(U.to_dev(Q, True), U.to_dev(K, True), U.to_dev(V, True), torch.from_numpy(off).cuda(),
