@@ -35,10 +35,17 @@ def _ptr(t: torch.Tensor | None) -> int | None:
     return None if t is None else t.data_ptr()
 
 
+# torch's own bindings (not public) give the current stream's handle itself: a
+# torch.cuda.Stream object for each of a round's calls costs more than the rest of the call's
+# arguments together.  A torch without them takes the public call.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream() -> int:
-    # the handle itself: a torch.cuda.Stream object for each of a round's calls costs more
-    # than the rest of the call's arguments together
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    if _raw_stream is None or _device is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(_device())
 
 
 def _need(t: torch.Tensor, name: str, dtype, shape=None):

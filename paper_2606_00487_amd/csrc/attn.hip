@@ -9,13 +9,13 @@
 //     owns one query column and the row max needs one exchange between lane halves;
 //   * O^T += V^T P^T: B = P^T comes straight from the S^T accumulators (converted to
 //     bf16); the key order inside the MFMA k-dimension follows the accumulator layout,
-//     and V is staged transposed in LDS in that order;
+//     and the transposing LDS read takes V's rows in that order;
 //   * K and V tiles are XOR-swizzled in LDS so the 16-byte reads of a wave hit distinct
 //     banks;
 //   * the ancestor-or-self bitmask of every node is rebuilt from parent pointers when a
 //     split reaches the tree rows; keys beyond the split or outside the mask get -inf;
-//   * fp32 online softmax in base 2; each split writes unnormalised O, its running max
-//     and its sum; a second kernel combines the splits and rounds to bf16.
+//   * fp32 online softmax in base 2; each split writes O / sum, its running max and its sum;
+//     a second kernel combines the splits and rounds to bf16.
 // (fp32 inputs: attn_f32.hip.)
 #include <algorithm>
 #include <cstdio>
@@ -1003,10 +1003,16 @@ __device__ __attribute__((always_inline)) inline void attn_bf16_body(
   //   matrix phase   S^T(t) = K(t) Q^T, O^T += V(t-1)^T P(t-1)^T: the operands are in
   //                  registers, and each is replaced by the next one's (K(t+1), V(t)) as soon
   //                  as its MFMA has been issued, so the LDS reads hide behind the MFMAs;
-  //   softmax phase  S(t) -> P(t): vector work alone.  Beside a busy matrix core a vector
-  //                  instruction takes 6 cycles and an exponential 11 (a microbenchmark), so
-  //                  this phase, about 75 of them, is the longer one: the slots are constant
+  //   softmax phase  S(t) -> P(t): vector work alone, about 75 instructions, 16 of them
+  //                  exponentials.  This phase is the longer one: the slots are constant
   //                  offsets (the loop is unrolled by four) and nothing else is left in it.
+  // Bound: the softmax phase and the change of phases.  Timestamps in a copy of the kernel (4
+  // x 32K keys, cycles): a matrix phase takes 550 (its 16 MFMAs 512), a softmax phase 700, and
+  // 270 go by from the longer phase's end to the next one's first instruction (the waits, the
+  // barrier, two load issues), so two stages, one of each wave, take 1940 and the matrix cores
+  // are busy for 53 % of them, at 1.91 GHz.  (A library product of 8192 keeps them busy for 69 %
+  // at 1.5 GHz.)  Paged: 2290 at 2.0 GHz, since a phase whose wave loads four blocks from a page
+  // starts 350 later.
   // Measured against the two waves in the same phase with their operands read before each
   // pair of MFMAs: 16 requests of 512-16K keys 228 -> 205 us, 4 x 32K keys over pages
   // 612 -> 577 us, one request of 128 nodes and 32K keys 83 -> 71 us (calls with the combine).

@@ -345,11 +345,13 @@ __global__ __launch_bounds__(256) void reduce_kernel(const float* __restrict__ p
 //   EP = kPartial: fp32 partials [split][M][N];  kBf16: one split, Y in bf16;
 //   kRope, kRopePaged: one split of the Q/K/V projection: RMSNorm, rotation and the stores of
 //   qkv_rope_kernel, from the accumulators (the tile is one head's 128 columns).
-// Bound: a stage of 256 rows is 1024 clocks of matrix instructions per SIMD and 48 KB of
-// direct loads, which the CU takes at 54 B/clk at most (a microbenchmark on cached rows), about
-// 900 clocks.  2048 x 4096 x 6144 takes ~110 us (0.94 PFLOP/s) and 2048 x 4096 x 4096 60 us (1.14
-// PFLOP/s; one exact round), against 180 + 32 (qkv_rope_kernel) and 119 + 9 us (reduce_kernel)
-// with 64-row tiles.
+// Bound: no single unit.  A stage of 256 rows takes about 2100 clocks (SQ counters; the matrix
+// cores are busy for 46 % of them), one of 128 rows 1460; their matrix instructions take 1024
+// and 512 per SIMD, their 48 and 32 KB of direct loads about 900 and 600 at the 54 B/clk that a
+// CU reaches on cached rows (a microbenchmark).  What the rest is has not been measured.
+// In one kernel trace of back-to-back layers (the clock at 1.9-2.1 GHz or below) 2048 x 4096 x
+// 6144 takes 139 + 5 us (rotation_kernel) and 2048 x 4096 x 4096 86 us, against 191 + 35
+// (qkv_rope_kernel) and 128 + 9 us (reduce_kernel) with 64-row tiles; on a cooler card 110 and 60.
 enum { kPartial = 0, kBf16 = 1, kRope = 2, kRopePaged = 3 };
 
 struct RopeOut {

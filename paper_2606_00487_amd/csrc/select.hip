@@ -1513,7 +1513,7 @@ hipError_t launch_select(const taps_select_params& p, const TopkPlan& plan, cons
     const RowLists lists{cand, zpart, spart, plan.chunks, p.K, p.kind, 0, p.beta, out.topk_idx,
                          out.topk_val};
     const size_t rows_dyn = learned_row_layout(p.block, p.K, mlp.d, mlp.h).bytes;
-    // more than 64 KB of LDS (13 KB of it static) is asked for explicitly
+    // more than 64 KB of LDS (9.3 KB of it static) is asked for explicitly
     if (rows_dyn > 48 * 1024 &&
         hipFuncSetAttribute((const void*)learned_rows_kernel,
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)rows_dyn) != hipSuccess)

@@ -282,8 +282,9 @@ __device__ inline bool fast_wave_topk_bf16(const void* rowp, int start, int end,
 
 // fp32 chunks, any length and alignment: the same filter as fast_wave_topk_bf16 on whole
 // 32-bit values.  The general path builds a key per element and compacts with one ballot per
-// register slot: 8 x 8 rows of 100001 took 41 us a selection call, 23.3 us so (4 x 8 rows of
-// 50257: 26.4 -> 23.4).  Same results and conditions.
+// register slot.  Selection calls by it and by this filter, chunks alike: 8 x 8 rows of 100001
+// 28.9 -> 20.4 us, 8 x 16 of 120000 35.7 -> 28.7, 4 x 8 of 50257 20.6 -> 17.7 (marginal scorer
+// 27.2 -> 24.0).  Same results and conditions.
 template <int E>
 __device__ inline bool fast_wave_topk_f32(const void* rowp, bool aligned, int start, int end,
                                           int tid, int K, uint64_t* s_wc, int* n_out) {
