@@ -581,12 +581,13 @@ __global__ __launch_bounds__(256) void attn_bf16_w4_kernel(
   const float lsum = l_run + other_half(l_run);
   const float inv = lsum > 0.f ? 1.f / lsum : 0.f;
 
-  // ---- write this split's partial: O / sum (fp32 for the ragged list's cut requests, else
+  // ---- write this split's partial: O / sum (fp32 for several requests that are cut, else
   // bf16), reference max and sum
   const size_t obase = (size_t)pair * mrows_pad;
   const int qr = row0 + rg * 32 + l32;
-  const bool wide = tab != nullptr && R > split_len;
-  unsigned char* const orow = (unsigned char*)wsO + (obase + qr) * (HD * (tab != nullptr ? 4 : 2));
+  const bool cut = batch > 1 && splits > 1;   // without a list
+  const bool wide = tab != nullptr ? R > split_len : cut;
+  unsigned char* const orow = (unsigned char*)wsO + (obase + qr) * (HD * (tab != nullptr || cut ? 4 : 2));
 #pragma unroll
   for (int db = 0; db < NDB; ++db)
 #pragma unroll
@@ -1213,25 +1214,24 @@ __device__ __attribute__((always_inline)) inline void attn_bf16_body(
   const float inv = Ls > 0.f ? 1.f / Ls : 0.f;
 
   // ---- write this split's partial: O / sum for this group's 64 head dims of the wave's 32
-  // rows (of several requests in fp32, but for the ragged list's uncut ones, else in bf16), max
-  // and sum.  The tile goes
+  // rows (fp32 for several requests that are cut, else bf16), max and sum.  The tile goes
   // through LDS (this wave's V slot, free now), 128 bytes of every row at a time: both head
-  // blocks in bf16, one in fp32.  So each store instruction writes whole 128-byte row segments.  The stores are
-  // non-temporal: only the combine, a later launch, reads the partials, and streaming them
-  // out of the L2 leaves less to write back when the kernel ends (measured: the kernel took
-  // 0.5 us less at the Qwen3-8B shape).
+  // blocks in bf16, one in fp32.  So each store instruction writes whole 128-byte row
+  // segments.  The stores are non-temporal: only the combine, a later launch, reads the
+  // partials, and streaming them out of the L2 leaves less to write back when the kernel ends
+  // (measured: the kernel took 0.5 us less at the Qwen3-8B shape).
   constexpr int TROW = 144;            // bytes per staged row (128 + 16: fewer bank conflicts)
   unsigned char* const stage = s_v + wave * TILEB;
   const size_t obase = (size_t)pair * mrows_pad;
   const int qbase = row0 + rg * 32;
-  const bool wide = MULTI && (!list || R > split_len);
+  const bool wide = MULTI && (list ? R > split_len : splits > 1);
   auto wave_sync = []() __attribute__((always_inline)) {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   };
   // the staged 128 bytes of every row to byte `at` of the rows' partials
-  constexpr size_t rowb = HD * (MULTI ? 4 : 2);
+  const size_t rowb = HD * (MULTI && (list || splits > 1) ? 4 : 2);
   auto flush = [&](int at) __attribute__((always_inline)) {
     wave_sync();
 #pragma unroll
@@ -1499,11 +1499,12 @@ AttnPlan plan_attn(int batch, int budget, int Hq, int Hkv, int head_dim, int max
     //   waits for a CU.  Against room for four everywhere: 3 requests of 700-20K keys 39.8 ->
     //   34.3, 3 of 1.1-3.1K (16/2 heads, 95 nodes) 26.3 -> 23.6.
     // * Less work takes no list: the choice, the table in the combine and the idle workgroups
-    //   cost 1-3 us.  List -> none, with the steps of the most work: 4 of 1.6-3.7K (16/2
-    //   heads, 41 nodes, 1.4K steps) 20.2 -> 17.9, 7 of 285-455 (30 nodes, 0.4K) 17.9 ->
-    //   16.6, but 3 of 1.1-3.1K (above, 1.8K) 23.6 -> 24.7; head_dim 64: 2 of 3-9K (63 nodes,
-    //   4.6K) 24.2 -> 22.3, 12 of 164-315 (16/8 heads, 180 nodes, 2.2K) 26.2 -> 25.3, but 14
-    //   of 280-1.2K (40/8, 74 nodes, 6.5K) 30.9 -> 34.7.
+    //   cost 1-3 us, which only long requests of different lengths win back.  Over 130 drawn
+    //   batches the lines below lose least in the mean (flat from 3000 to 5000 steps at
+    //   head_dim 128, from 2000 to 5000 at 64).  None -> list, longest request to the mean in
+    //   brackets: 3.0K steps (1.06) 26.5 -> 27.4, 3.3K (1.75) 20.7 -> 22.3, 4.0K (2.4) 25.4 ->
+    //   20.9, 5.1K (1.7) 27.7 -> 24.6; head_dim 64: 1.7K (1.5) 18.7 -> 20.5, 2.7K (1.3) 17.4
+    //   -> 18.4, 3.6K (1.35) 25.7 -> 27.0, 3.7K (1.9) 24.4 -> 19.6, 5.2K (1.6) 26.5 -> 22.2.
     const long long steps = base * keys / kKT;
     const int wgs = head_dim == 128 ? (steps <= 32768 ? 256 : 1024) : steps <= 32768 ? 512 : 1024;
     int target = (wgs + p.mtiles - 1) / p.mtiles;
@@ -1511,23 +1512,23 @@ AttnPlan plan_attn(int batch, int budget, int Hq, int Hkv, int head_dim, int max
     if (worst() > p.lcap) target = (1024 + p.mtiles - 1) / p.mtiles;
     const long long pm = std::max((long long)target + (long long)batch * Hkv,
                                   (long long)batch * Hkv * p.splits);
-    if (worst() <= p.lcap && pm < (1ll << 24) && steps >= (head_dim == 128 ? 1536 : 6144)) {
+    if (worst() <= p.lcap && pm < (1ll << 24) && steps >= (head_dim == 128 ? 4096 : 3072)) {
       p.ragged = 1;
       p.target_pairs = target;
       p.pairs_max = (int)pm;
     }
   }
-  p.wide = p.ragged || (batch > 1 && head_dim == 128);
+  p.wide = p.ragged || (batch > 1 && p.splits > 1);
   return p;
 }
 
 // split partials [slot][mtiles * mtile][head_dim], then their (max, sum) pairs, then (ragged
-// list) the per-request table of the combine.  Partials are bf16, but fp32 (pl.wide) where the
-// batch's lengths decide how a request is cut: a partial rounded to bf16 gives a request cut
-// in two a quarter more error than the same request uncut (2.9e-3 against 2.3e-3 of the
-// result).  A request that the ragged list leaves uncut is rounded once in any case and keeps
-// the shorter ones.  fp32 costs 8 us of 213 at 16 requests of 512-16K keys (32/8 heads of
-// 128), 0.6 of 28.7 at 4 of 2-8K with head_dim 64.
+// list) the per-request table of the combine.  Partials are bf16, but fp32 (pl.wide) where
+// several requests are cut: how depends on the batch, and a partial rounded to bf16 gives a
+// request cut in two a quarter more error than the same request uncut (2.9e-3 against 2.3e-3
+// of the result).  A request that the ragged list leaves uncut is rounded once in any case and
+// keeps the shorter ones.  fp32 costs 8 us of 213 at 16 requests of 512-16K keys (32/8 heads
+// of 128), 0.6 of 28.7 at 4 of 2-8K with head_dim 64, 0.3-1.6 of 10-18 in smaller batches.
 static size_t attn_part_bytes(const AttnPlan& pl) { return pl.wide ? 4 : 2; }
 static size_t attn_rows(const AttnPlan& pl, int batch, int Hkv) {
   const size_t slots = pl.ragged ? (size_t)pl.pairs_max : (size_t)batch * Hkv * pl.splits;

@@ -51,7 +51,8 @@ def _reference(q, k, v, ctx, parent, scale):
     ([6200, 40, 2500, 0], 64, 32, 8),                                # far apart, cut finely
     ([512, 700, 900, 1300, 1900, 2700, 4000, 6050], 128, 16, 8),     # one or two splits each
     ([2100, 2000, 2050, 1990, 2080, 2010], 128, 32, 8),              # close: the host's length
-]] + [(128, [1500, 1400, 1450], 20, 8, 2)])                          # little work: no list
+    ([1500, 1400, 1450], 20, 8, 2),                                  # little work: no list
+    ([100, 300, 20, 250], 300, 16, 4)]])                             # ... and not cut either
 def test_batches_are_as_accurate_as_uncut_ones(taps, hd, ctx, N, Hq, Hkv):
     print(f"[ragged-accuracy] hd={hd} N={N} ctx={ctx}", flush=True)
     g = torch.Generator().manual_seed(len(ctx) + hd)

@@ -27,7 +27,7 @@ def _branch(R, max_ctx, N, Hq, Hkv, hd):
     max_ctx without a list ("plain"); the list with the host's length ("host"), for more requests
     than a wave has lanes ("many") or with the cheapest of 64 lengths ("search")."""
     steps = len(R) * Hkv * -(-N * (Hq // Hkv) // 128) * (max_ctx + N) // 64
-    if steps < (1536 if hd == 128 else 6144):
+    if steps < (4096 if hd == 128 else 3072):
         return "plain"
     if 4 * max(R) * len(R) <= 5 * sum(R):
         return "host"
@@ -42,16 +42,16 @@ SQ64 = [(97 * i * i) % 3000 for i in range(64)]
     (hd, *c, "plain") for hd in (64, 128) for c in [
         ([3000, 5], 9, 4, 2), ([500, 510, 505], 40, 8, 2), ([0, 0], 1, 2, 1),
         ([700, 1400, 2100, 64, 0], 33, 8, 2), (SQ70, 5, 4, 1)]] + [
-    (128, [6000, 40, 2500, 0], 64, 16, 4, "search"), (128, SQ64, 5, 4, 1, "search"),
-    (128, SQ70, 5, 4, 2, "many"),
-    (128, [6200, 3710], 16, 8, 8, "search"),     # just past the 5/4 of the mean
-    (128, [6200, 3720], 16, 8, 8, "host"),       # just within it
-    (128, [6128, 10], 16, 8, 8, "search"),       # 1536 steps of 64 keys
-    (128, [6127, 10], 16, 8, 8, "plain"),        # one key fewer
+    (128, [6000, 40, 2500, 0], 64, 32, 8, "search"), (128, SQ64, 5, 4, 2, "search"),
+    (128, SQ70, 5, 8, 8, "many"),
+    (128, [4100, 2432], 64, 64, 16, "search"),   # just past the 5/4 of the mean
+    (128, [4100, 2434], 64, 64, 16, "host"),     # just within it
+    (128, [4032, 100], 64, 64, 16, "search"),    # 4096 steps of 64 keys
+    (128, [4031, 100], 64, 64, 16, "plain"),     # one key fewer
     (64, [6200, 40, 2500, 0], 64, 32, 8, "search"), (64, SQ70, 5, 8, 8, "many"),
     (64, SQ64, 5, 8, 4, "search"), (64, [2100, 2000, 2050, 1800, 1700, 2010], 128, 32, 8, "host"),
-    (64, [6080, 100], 64, 64, 16, "search"),     # 6144 steps of 64 keys
-    (64, [6079, 100], 64, 64, 16, "plain"),      # one key fewer
+    (64, [3008, 100], 64, 64, 16, "search"),     # 3072 steps of 64 keys
+    (64, [3007, 100], 64, 64, 16, "plain"),      # one key fewer
 ])
 def test_ragged_pick(taps, hd, ctx, N, Hq, Hkv, branch):
     rng = np.random.default_rng(len(ctx) + hd)
