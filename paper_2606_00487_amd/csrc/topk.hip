@@ -492,8 +492,9 @@ hipError_t launch_dt(const void* marg, int rows, int vocab, int K, const TopkPla
 
 TopkPlan plan_topk(int vocab, int rows, int dtype, bool z) {
   // aim for ~512 workgroups; chunks of 2048..16384 elements (8..64 per thread).  64 elements
-  // a thread need 190 registers, so two waves per SIMD or two workgroups per CU: with more
-  // workgroups, chunks of 8192 take their place.  Selection calls in us, 16384 -> 8192:
+  // a thread need 190 registers, so two waves per SIMD or two workgroups per CU: with more than
+  // 1.5 such workgroups per CU, chunks of 8192 take their place.  Selection calls in us, 16384
+  // -> 8192:
   //   bf16 rows that fast_wave_topk_bf16 takes, K = 4 / 8 / 16: 16 x 16 rows of 151936
   //     36.1 -> 33.9 / 43.1 -> 40.2 / 57.2 -> 53.2, 4 x 32 rows 28.1 -> 26.9 / 35.0 -> 33.6 /
   //     51.2 -> 47.6, 8 x 16 of 262144 32.1 -> 31.2 / 38.2 -> 37.0 / 48.0 -> 46.4, 32 x 8 of
@@ -502,15 +503,14 @@ TopkPlan plan_topk(int vocab, int rows, int dtype, bool z) {
   //   the same with the normaliser pass, whose fp64 sums have one more start per chunk: 8 x 16
   //     of 262144 84.0 -> 88.8 / 89.9 -> 94.6 / 97.6 -> 102.0, 16 x 16 of 151936 99.8 -> 101.4
   //     / 105.5 -> 106.6 / 118.9 -> 118.3: they keep 16384;
-  //   fp32, and bf16 rows of the general path, gain from 1.5 workgroups per CU on: 8 x 16 rows
-  //     of 120000 fp32 31.1 -> 27.5, 12 x 8 of 65537 fp32 32.2 -> 27.7, 8 x 8 of 128257 bf16
-  //     36.9 -> 32.1, 8 x 12 of 60000 (1.5 per CU) 37.7 -> 38.1.
+  //   fp32, and bf16 rows of the general path: 8 x 16 rows of 120000 fp32 31.1 -> 27.5, 12 x 8
+  //     of 65537 fp32 32.2 -> 27.7, 8 x 8 of 128257 bf16 36.9 -> 32.1, 8 x 12 of 60000 (1.5
+  //     per CU) 37.7 -> 38.1.
   // The lists of 16384 chunks stay far below the static scratch of the noalloc call, whose
   // limit the longer chunks therefore still set.
   const int target_chunks = rows >= 512 ? 1 : (512 + rows - 1) / rows;
   const bool filter16 = dtype == TAPS_BF16 && vocab % 8 == 0;
-  const bool filled =
-      (int64_t)rows * ((vocab + 16383) / 16384) > (filter16 ? 512 : 384) && !(filter16 && z);
+  const bool filled = (int64_t)rows * ((vocab + 16383) / 16384) > 384 && !(filter16 && z);
   const int most = filled && (int64_t)rows * ((vocab + 8191) / 8192) <= 16384 ? 8192 : 16384;
   int len = 2048;
   while (len < 16384 && ((len < most && (int64_t)len * target_chunks < vocab) ||

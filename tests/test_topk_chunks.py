@@ -1,6 +1,6 @@
 """The vocabulary scan's chunk length on each side of its rule, read off the scratch that a call
-asks for (host only): 8192 where more workgroups of 16384 than the chip holds at once would
-scan, but not for bf16 rows whose full-vocabulary sums are taken chunk by chunk as well."""
+asks for (host only): 8192 where more than 384 workgroups of 16384 would scan, but not for bf16
+rows whose full-vocabulary sums are taken chunk by chunk as well."""
 import ctypes
 
 import pytest
@@ -28,10 +28,10 @@ def _chunks(batch, block, vocab, K, dtype, scorer):
     (8, 16, 262144, BF16, LEARNED, 16384),
     (8, 16, 262144, FP32, MARGINAL, 8192),
     (8, 16, 262143, BF16, MARGINAL, 8192),     # rows of the general path
-    (8, 8, 131072, BF16, SIBLING, 16384),      # just two workgroups per CU
-    (8, 8, 131073, FP32, SIBLING, 8192),
-    (3, 19, 147456, BF16, SIBLING, 8192),      # 513 of them
-    (4, 8, 196608, FP32, SIBLING, 16384),      # 384 of them
+    (4, 8, 196608, BF16, SIBLING, 16384),      # 384 workgroups
+    (4, 8, 196616, BF16, SIBLING, 8192),       # more
+    (4, 8, 196608, FP32, MARGINAL, 16384),
+    (4, 8, 196609, FP32, MARGINAL, 8192),
     (16, 32, 300000, BF16, SIBLING, 16384),    # 8192 would leave more than 16384 lists
 ])
 def test_chunk_length(batch, block, vocab, dtype, scorer, length, K):
